@@ -101,6 +101,16 @@ __host__ __device__ inline double sqrt_(double x)
     return sqrt(x);
 #endif
 }
+// Estimate of 1 / sqrt(x) to about 1e-7 (the device's instruction); NaN for
+// x < 0, infinite for 0.
+__host__ __device__ inline double rsq_estimate(double x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __builtin_amdgcn_rsq(x);
+#else
+    return 1.0 / sqrt(x);
+#endif
+}
 // reciprocal square root (the device uses the hardware estimate refined by
 // the math library; the host path only serves host-side tools)
 __host__ __device__ inline float rsqrt_(float x)

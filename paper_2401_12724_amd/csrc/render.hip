@@ -3,7 +3,7 @@
 //
 // One wavefront pass renders spp_batch samples of every pixel of the crop;
 // each path owns a radiance slot for the whole pass.  Per bounce:
-//   k_r_extend  one ray per lane (LDS traversal stack): yarn BVH, the light
+//   k_r_extend  one ray per lane, searched by four lanes each: yarn BVH, the light
 //               rectangle, the environment; light / environment hits add
 //               their radiance to the path's slot and end it
 //   k_r_shade   BYSDF at the hit (wave-uniform type): one state at x and one
@@ -56,7 +56,8 @@ static int fail(int code, const char* fmt, ...)
 
 namespace {
 
-constexpr int kTraceBlock = 128;
+constexpr int kTraceBlock = 64;
+constexpr int kTraceWaves = kTraceBlock / 64;
 constexpr int kShadeBlock = 256;
 constexpr int kMaxPassThrough = 16;
 constexpr uint32_t kSampleFail = 1u << 6;
@@ -190,17 +191,24 @@ __global__ __launch_bounds__(kTraceBlock, RENDER_TRACE_MIN_WAVES) void k_r_exten
                                                                                   const int* cnt_in, HitQ H,
                                                                                   float* L, int cap, int depth)
 {
-    extern __shared__ int stk[];  // yarn::stack_entries(BVH depth) x kTraceBlock
-    int* my = stk + threadIdx.x;
-    const int n = *cnt_in;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        D3 o = yarn::d3(Q.ox[i], Q.oy[i], Q.oz[i]);
-        D3 d = yarn::unit(yarn::d3(Q.dx[i], Q.dy[i], Q.dz[i]));
-        const double tmin = depth == 0 ? 0.0 : V.eps;
-        const int lid = Q.lid[i], skip = Q.skip[i];
-        int ex[yarn::kMaxExcluded + 1];
-        int nex = yarn::excluded_yarns(V.S, o, my, kTraceBlock, ex, skip);
-        yarn::RayHit hit = yarn::closest_hit(V.S, o, d, tmin, 1e30, ex, nex, my, kTraceBlock);
+    __shared__ yarn::WaveRays s_rays[kTraceWaves];
+    extern __shared__ int stk[];  // per wavefront V.S.stack x kWaveRays
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    yarn::WaveRays& W = s_rays[wave];
+    int* my = stk + wave * V.S.stack * yarn::kWaveRays;
+    const int n = *cnt_in, per = yarn::rays_per_wave(n);
+    const double tmin = depth == 0 ? 0.0 : V.eps;
+    for (int i0 = (blockIdx.x * kTraceWaves + wave) * per; i0 < n; i0 += gridDim.x * kTraceWaves * per) {
+        const int i = i0 + lane;
+        const bool in = lane < per && i < n;
+        if (in)
+            W.set(lane, yarn::d3(Q.ox[i], Q.oy[i], Q.oz[i]), yarn::unit(yarn::d3(Q.dx[i], Q.dy[i], Q.dz[i])), 1e30,
+                  Q.skip[i]);
+        int n_ex;
+        const yarn::RayHit hit = yarn::trace_wave(V.S, W, my, in, tmin, n_ex);
+        if (!in) continue;
+        const D3 o = W.origin(lane), d = W.dir(lane);
+        const int lid = Q.lid[i];
         // the light: one-sided rectangle
         D3 ln = dv(V.ln);
         double den = yarn::dot(d, ln), tl = INFINITY;
@@ -625,22 +633,28 @@ __global__ __launch_bounds__(kTraceBlock, RENDER_TRACE_MIN_WAVES) void k_r_shado
 {
     bysdf::stage_math_tables();
     __syncthreads();
-    extern __shared__ int stk[];  // yarn::stack_entries(BVH depth) x kTraceBlock
-    int* my = stk + threadIdx.x;
-    const int n = *cnt;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        D3 o = yarn::d3(SQ.ox[i], SQ.oy[i], SQ.oz[i]);
-        D3 d = yarn::unit(yarn::d3(SQ.dx[i], SQ.dy[i], SQ.dz[i]));
-        double tmax = SQ.tmax[i];
-        int skip = SQ.skip[i];
-        bool visible = false;
-        for (int k = 0; k < kMaxPassThrough; ++k) {
-            int ex[yarn::kMaxExcluded + 1];
-            int nex = yarn::excluded_yarns(V.S, o, my, kTraceBlock, ex, skip);
-            yarn::RayHit hit = yarn::closest_hit(V.S, o, d, V.eps, tmax, ex, nex, my, kTraceBlock);
+    __shared__ yarn::WaveRays s_rays[kTraceWaves];
+    extern __shared__ int stk[];  // per wavefront V.S.stack x kWaveRays
+    const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
+    yarn::WaveRays& W = s_rays[wave];
+    int* my = stk + wave * V.S.stack * yarn::kWaveRays;
+    const int n = *cnt, per = yarn::rays_per_wave(n);
+    for (int i0 = (blockIdx.x * kTraceWaves + wave) * per; i0 < n; i0 += gridDim.x * kTraceWaves * per) {
+        const int i = i0 + lane;
+        const bool in = lane < per && i < n;
+        if (in)
+            W.set(lane, yarn::d3(SQ.ox[i], SQ.oy[i], SQ.oz[i]), yarn::unit(yarn::d3(SQ.dx[i], SQ.dy[i], SQ.dz[i])),
+                  SQ.tmax[i], SQ.skip[i]);
+        bool visible = false, live = in;
+        for (int k = 0; k < kMaxPassThrough && __any((int)live); ++k) {
+            int n_ex;
+            const yarn::RayHit hit = yarn::trace_wave(V.S, W, my, live, V.eps, n_ex);
+            if (!live) continue;
+            const D3 o = W.origin(lane), d = W.dir(lane);
             if (hit.span < 0) {
                 visible = true;
-                break;
+                live = false;
+                continue;
             }
             yarn::SpanRec r = V.S.span[hit.span];
             yarn::HitFrame fr = yarn::hit_frame(V.S, hit.span, hit.s);
@@ -660,17 +674,20 @@ __global__ __launch_bounds__(kTraceBlock, RENDER_TRACE_MIN_WAVES) void k_r_shado
             const Derived<double, float>& P = V.types[V.S.yarn_type[r.yarn]].d;
             PlyHit<double, MP> ph;
             bysdf::trace_plies(P, h, V.S.yarn_phase[r.yarn], vl, wi, ph);
-            if (!ph.pass) break;
+            if (!ph.pass) {
+                live = false;
+                continue;
+            }
             double sxy = sqrt((double)wi.x * wi.x + (double)wi.y * wi.y);
             double ch = 2.0 * R * sqrt(fmax(0.0, 1.0 - (double)h * h)) / fmax(sxy, 1e-12);
             D3 on = p + d * ch;
-            o = yarn::d3((float)on.x, (float)on.y, (float)on.z);
-            tmax -= (double)th + ch;
+            const double tmax = W.t_max[lane] - ((double)th + ch);
             if (tmax <= 0.0) {
                 visible = true;
-                break;
+                live = false;
+                continue;
             }
-            skip = r.yarn;
+            W.move(lane, on, tmax, r.yarn);
         }
         if (visible) {
             const int lid = SQ.lid[i];
@@ -897,6 +914,9 @@ static int render(const yarn_scene_t* scene, const bysdf_types_t* types, const r
         int64_t g = (n + block - 1) / block;
         return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, cap_blocks));
     };
+    // a wavefront visits rays_per_wave of the queue's actual length, which only
+    // the device knows: enough for the full queue's visits or 16-ray visits
+    auto trace_grid = [&](int64_t n) { return grid_for(n, kTraceWaves * yarn::rays_per_wave(n), 65536); };
     hipLaunchKernelGGL(k_r_fill, dim3(grid_for(3 * (int64_t)npix, 256, 4096)), dim3(256), 0, stream, fb,
                        3 * (int64_t)npix);
     if (g)
@@ -904,9 +924,7 @@ static int render(const yarn_scene_t* scene, const bysdf_types_t* types, const r
                            kGrad * (int64_t)npix);
     hipLaunchKernelGGL(k_r_fill, dim3(1), dim3(256), 0, stream, (float*)stats, (int64_t)4);
     const bool mp4 = tv.max_plies <= 4;
-    int64_t sinfo[6];
-    if (int rc = yarn_scene_info(scene, sinfo)) return rc;
-    const size_t stk_bytes = sizeof(int) * yarn::stack_entries((int)sinfo[4]) * kTraceBlock;
+    const size_t stk_bytes = yarn::stack_bytes(V.S.stack, kTraceBlock);
     for (int j0 = 0; j0 < rs->spp; j0 += spp_batch) {
         const int nb = std::min(spp_batch, rs->spp - j0);
         const int n = npix * nb;
@@ -915,7 +933,7 @@ static int render(const yarn_scene_t* scene, const bysdf_types_t* types, const r
         for (int depth = 0; depth <= rs->max_depth; ++depth) {
             const int a = depth & 1, b = a ^ 1;
             hipLaunchKernelGGL(k_r_tally, dim3(1), dim3(64), 0, stream, cnt, a, stats, 0);
-            hipLaunchKernelGGL(k_r_extend, dim3(grid_for(n, kTraceBlock, 16384)), dim3(kTraceBlock), stk_bytes,
+            hipLaunchKernelGGL(k_r_extend, dim3(trace_grid(n)), dim3(kTraceBlock), stk_bytes,
                                stream, V, Qs[a], cnt + a, Hh, L, n, depth);
             if (depth == rs->max_depth) break;
             hipLaunchKernelGGL(k_r_counters, dim3(1), dim3(64), 0, stream, cnt, b, 2, -1);
@@ -931,7 +949,7 @@ static int render(const yarn_scene_t* scene, const bysdf_types_t* types, const r
             hipLaunchKernelGGL(shade, dim3(grid_for(n, kShadeBlock, 8192)), dim3(kShadeBlock), 0, stream, Vs,
                                Qs[a], cnt + a, Hh, Qs[b], cnt + b, SQ, cnt + 2, n, depth, j0, nb);
             hipLaunchKernelGGL(k_r_tally, dim3(1), dim3(64), 0, stream, cnt, 2, stats, 1);
-            hipLaunchKernelGGL(mp4 ? k_r_shadow<4> : k_r_shadow<8>, dim3(grid_for(n, kTraceBlock, 16384)),
+            hipLaunchKernelGGL(mp4 ? k_r_shadow<4> : k_r_shadow<8>, dim3(trace_grid(n)),
                                dim3(kTraceBlock), stk_bytes, stream, V, SQ, cnt + 2, L, n);
         }
         hipLaunchKernelGGL(k_r_accum, dim3(grid_for(npix, 256, 4096)), dim3(256), 0, stream, L, fb, grad, npix, nb,

@@ -11,6 +11,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstring>
 #include <exception>
 #include <string>
 #include <system_error>
@@ -366,26 +367,18 @@ struct Collapse {
         int code[4];
         for (int k = 0; k < nch; ++k) code[k] = ch[k].code >= 0 ? run(ch[k].code, depth + 1) : ch[k].code;
         WNode& w = wide[self];
-        float lo[3][4], hi[3][4];
-        int cw[4];
         for (int k = 0; k < 4; ++k) {
             // an unused slot, or a slot with an inverted box, is never entered
             bool empty = k >= nch;
             for (int q = 0; q < 3 && !empty; ++q) empty = !(ch[k].lo[q] <= ch[k].hi[q]);
-            for (int q = 0; q < 3; ++q) {
-                lo[q][k] = empty ? INFINITY : ch[k].lo[q];
-                hi[q][k] = empty ? INFINITY : ch[k].hi[q];
-            }
-            cw[k] = empty ? 0 : code[k];
+            const int cw = empty ? 0 : code[k];
+            float cf;
+            memcpy(&cf, &cw, sizeof cf);
+            w.child[k].lo_code = empty ? make_float4(INFINITY, INFINITY, INFINITY, cf)
+                                       : make_float4(ch[k].lo[0], ch[k].lo[1], ch[k].lo[2], cf);
+            w.child[k].hi_yarn = empty ? make_float4(INFINITY, INFINITY, INFINITY, 0.f)
+                                       : make_float4(ch[k].hi[0], ch[k].hi[1], ch[k].hi[2], 0.f);
         }
-        w.lox = make_float4(lo[0][0], lo[0][1], lo[0][2], lo[0][3]);
-        w.loy = make_float4(lo[1][0], lo[1][1], lo[1][2], lo[1][3]);
-        w.loz = make_float4(lo[2][0], lo[2][1], lo[2][2], lo[2][3]);
-        w.hix = make_float4(hi[0][0], hi[0][1], hi[0][2], hi[0][3]);
-        w.hiy = make_float4(hi[1][0], hi[1][1], hi[1][2], hi[1][3]);
-        w.hiz = make_float4(hi[2][0], hi[2][1], hi[2][2], hi[2][3]);
-        w.code = make_int4(cw[0], cw[1], cw[2], cw[3]);
-        w.pad = make_int4(0, 0, 0, 0);
         return self;
     }
 };
@@ -545,6 +538,19 @@ inline int yarn_scene_build_host(const float* ctrl, const int64_t* off, int32_t 
     if (W.max_depth > kWideDepthMax)
         return build_fail(err, BYSDF_ERR_INVALID_PARAM, "4-wide BVH depth %d exceeds %d", W.max_depth,
                           kWideDepthMax);
+    for (WNode& w : W.wide)
+        for (WChild& c : w.child) {
+            int code, yarn = -1;
+            memcpy(&code, &c.lo_code.w, sizeof code);
+            if (code < 0) {
+                int first, count;
+                decode_leaf(code, &first, &count);
+                yarn = rec_o[first].yarn;
+                for (int k = 1; k < count; ++k)
+                    if (rec_o[first + k].yarn != yarn) yarn = -1;
+            }
+            memcpy(&c.hi_yarn.w, &yarn, sizeof yarn);
+        }
     hs->node = std::move(W.wide);
     hs->depth = W.max_depth;
     hs->n_yarns = n_yarns;

@@ -8,8 +8,9 @@
 // median splits below depth 40, collapsed to four children per node.
 // Spans are stored in leaf order next to their records.
 //
-// Kernel k_intersect: one ray per lane, 128-lane workgroups, an LDS stack
-// per lane ([entry][lane], no bank conflicts) of 3 (depth + 1) entries.  A point query
+// Kernel k_intersect: a wavefront takes up to 64 rays and searches 16 at a
+// time, four lanes per ray, with an LDS stack per ray ([entry][ray]) of
+// 3 (depth + 1) entries.  A point query
 // first collects the yarns whose tube holds the origin, then the closest
 // entering hit is searched; hit frame, h and v are formed for the winner.
 #include <hip/hip_runtime.h>
@@ -72,12 +73,13 @@ struct yarn_scene {
         v.yarn_phase = d_phase;
         v.yarn_type = d_type;
         v.n_nodes = (int)n_nodes;
+        v.stack = stack_entries(depth);
         return v;
     }
 };
 
 // ------------------------------------------------------------ kernel
-constexpr int kIsectBlock = 128;
+constexpr int kIsectBlock = 64;
 
 #ifndef YARN_ISECT_MIN_WAVES
 #define YARN_ISECT_MIN_WAVES 3
@@ -86,10 +88,14 @@ __global__ __launch_bounds__(kIsectBlock, YARN_ISECT_MIN_WAVES) void k_intersect
                                                                                  int64_t n, double t_min,
                                                                                  yarn_hit_soa H)
 {
-    extern __shared__ int stk[];  // stack_entries(depth) x kIsectBlock
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        intersect_ray(S, i, R, t_min, H, stk + threadIdx.x, kIsectBlock);
+    __shared__ WaveRays s_rays[kIsectBlock / 64];
+    extern __shared__ int stk[];  // per wavefront stack_entries(depth) x kWaveRays
+    const int wave = threadIdx.x / 64;
+    const int per = rays_per_wave(n);
+    const int64_t w0 = blockIdx.x * (int64_t)(kIsectBlock / 64) + wave, stride = gridDim.x * (int64_t)(kIsectBlock / 64);
+    int* my = stk + wave * S.stack * kWaveRays;
+    for (int64_t i = w0 * per; i < n; i += stride * per)
+        intersect_rays(S, i, (int)min((int64_t)per, n - i), R, t_min, H, s_rays[wave], my);
 }
 
 // ------------------------------------------------------------ C ABI
@@ -222,10 +228,11 @@ extern "C" int yarn_tube_intersect(const yarn_scene_t* s, const yarn_ray_soa* ra
     for (const void* p : o)
         if (!p || ((uintptr_t)p & 3u)) return fail(BYSDF_ERR_INVALID_ARG, "hit arrays must be non-NULL and 4-byte aligned");
     if (!std::isfinite(t_min)) return fail(BYSDF_ERR_INVALID_ARG, "t_min must be finite");
-    int64_t blocks = (n + kIsectBlock - 1) / kIsectBlock;
+    const int64_t per = kIsectBlock / 64 * rays_per_wave(n);
+    int64_t blocks = (n + per - 1) / per;
     if (blocks > 65536 * 8) blocks = 65536 * 8;
     hipLaunchKernelGGL(k_intersect, dim3((unsigned)blocks), dim3(kIsectBlock),
-                       sizeof(int) * stack_entries(s->depth) * kIsectBlock, stream, s->view(), *rays, n,
+                       stack_bytes(stack_entries(s->depth), kIsectBlock), stream, s->view(), *rays, n,
                        (double)t_min, *hits);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(BYSDF_ERR_LAUNCH, "k_intersect: %s", hipGetErrorString(e));

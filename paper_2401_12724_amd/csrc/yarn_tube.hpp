@@ -11,14 +11,13 @@
 // safeguarded Newton on dT/ds in double precision.
 //
 // The BVH is built binary (binned SAH) and collapsed to four children per
-// node: a node holds its four child boxes as structure of arrays and the
-// child codes in one 128-byte line, so a ray fetches half as many nodes
-// one after another as in the binary tree.  Hit children are visited near
-// first, and the per-thread stack lives in LDS.  The closest-hit traversal
-// runs nodes and span scans in separate loops, with postponed leaves, so
-// the span scans of a wavefront run together; the point query for tubes
-// holding the origin stops each span's distance test as soon as a sample
-// decides it.
+// node, so a ray fetches half as many nodes one after another as in the
+// binary tree; each ray is traced by the four lanes of a quad, one child or
+// span per lane.  Hit children are visited near first, and the per-ray stack
+// lives in LDS.  The closest-hit traversal runs nodes and span scans in
+// separate loops, with postponed leaves, so the span scans of a wavefront
+// run together; the point query for tubes holding the origin stops each
+// span's distance test as soon as a sample decides it.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,12 +31,14 @@ namespace yarn {
 
 constexpr int kStack = 64;        // binary BVH depth bound enforced by the builder
 constexpr int kWideDepthMax = 40; // depth bound of the 4-wide tree (LDS stack: 123 entries)
-// Entries of a lane's traversal stack for a 4-wide BVH whose deepest node
+// Entries of a ray's traversal stack for a 4-wide BVH whose deepest node
 // sits at the given depth (root 0): a visit pushes at most three siblings,
 // and a path holds depth + 1 nodes, so 3 (depth + 1) entries never
-// overflow.  The traversal kernels size their LDS stacks with this at
-// launch, which leaves LDS for more wavefronts per CU on shallow trees.
+// overflow.  The traversal kernels size their LDS stacks with this at launch.
 inline int stack_entries(int depth) { return 3 * (depth + 1); }
+constexpr int kWaveRays = 16;     // rays a wavefront traces side by side
+// LDS bytes of the stacks of a traversal workgroup of `block` lanes
+inline size_t stack_bytes(int entries, int block) { return sizeof(int) * entries * kWaveRays * (block / 64); }
 constexpr int kMaxExcluded = 4;   // yarns holding the ray origin
 constexpr double kExcludeFrac = 1e-3;
 
@@ -53,12 +54,18 @@ struct BNode {
     float4 a, b, c;
     int4 d;
 };
-// node of the traversed 4-wide tree: bounds of child c in component c of
-// each float4; an unused slot has an empty box (lo +inf, hi -inf)
+// node of the traversed 4-wide tree: one 32-byte record per child, read by
+// one lane each (two 16-byte loads; a quad reads the node's 128-byte line).
+// lo_code.w holds the child's code as above (node codes index the wide
+// nodes), hi_yarn.w the yarn of a leaf whose spans are all of one yarn (-1
+// otherwise: consecutive spans of a yarn share a leaf, and a ray that leaves
+// a yarn passes its leaves by without scanning them); an unused slot has an
+// empty box (lo and hi +inf)
+struct WChild {
+    float4 lo_code, hi_yarn;
+};
 struct WNode {
-    float4 lox, loy, loz, hix, hiy, hiz;
-    int4 code;  // child codes as above (node codes index the wide nodes)
-    int4 pad;   // to 128 bytes
+    WChild child[4];
 };
 
 // span record (leaf order): first control point, yarn, index in the
@@ -75,6 +82,7 @@ struct SceneView {
     const float* yarn_phase;
     const int* yarn_type;
     int n_nodes;
+    int stack;  // entries of a ray's traversal stack
 };
 
 struct D3 {
@@ -178,11 +186,16 @@ __host__ __device__ inline bool entry_slope(const RayCubic& rc, double R, double
     return true;
 }
 
-// Sampled scan of one span: the smallest entry T(s_i) > t_min over the
-// nsamp + 1 samples, if it is at most t_lim (and the control-point hull
-// reaches the ray's R-slab within [t_min, t_lim + R]).
-__host__ __device__ inline bool span_scan(const SpanGeo& g, D3 d, D3 e1, D3 e2, double t_min, double t_lim,
-                                          int nsamp, double* t_out, int* i_out)
+// A span to sample: its view from the ray, R^2 and 1 / samples.
+struct SpanView {
+    RayCubic rc;
+    double R2, inv;
+};
+
+// Whether a span may be entered at t_min < t <= t_lim: false when the hull of
+// its control points misses the ray's R-slab in that range.  Fills its view.
+__device__ inline bool span_view(const SpanGeo& g, D3 d, D3 e1, D3 e2, double t_min, double t_lim, int nsamp,
+                                 SpanView* v)
 {
     const double R = g.R;
     bool all_pu = true, all_nu = true, all_pw = true, all_nw = true, all_b = true, all_f = true;
@@ -203,45 +216,79 @@ __host__ __device__ inline bool span_scan(const SpanGeo& g, D3 d, D3 e1, D3 e2, 
     if (all_pu || all_nu || all_pw || all_nw || all_b || all_f) return false;
     // the curve lies in the hull of its control points: in the plane across
     // the ray, a hull entirely more than R to one side of the line through
-    // the outer two points' direction (the span's chord) misses the ray
+    // the outer two points' direction (the span's chord) misses the ray; the
+    // outer points are equally far from that line
     {
-        double cx = pu[3] - pu[0], cy = pw[3] - pw[0];
-        double cl = bysdf::sqrt_(cx * cx + cy * cy);
-        if (cl > 1e-12 * R) {
-            const double icl = bysdf::rcp_(cl);
-            double nx = -cy * icl, ny = cx * icl;
-            bool all_p = true, all_n = true;
+        const double cx = pu[3] - pu[0], cy = pw[3] - pw[0];
+        const double rl = R * bysdf::sqrt_(cx * cx + cy * cy);
+        bool all_p = true, all_n = true;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                double sd = nx * pu[k] + ny * pw[k];
-                all_p &= sd > R;
-                all_n &= sd < -R;
-            }
-            if (all_p || all_n) return false;
+        for (int k = 0; k < 3; ++k) {
+            const double sd = cx * pw[k] - cy * pu[k];
+            all_p &= sd > rl;
+            all_n &= sd < -rl;
         }
+        if (rl > 1e-12 * R * R && (all_p || all_n)) return false;
     }
-    // the samples in the ray's frame (e1, e2, d): the centreline's offset
-    // (u, w) from the ray and its position z along it are cubics in s, in
-    // power form from the projected control points, so a sample costs three
-    // Horner steps per coordinate and r^2 = u^2 + w^2 has no cancellation
-    RayCubic rc;
-    spline_power(pu, rc.u);
-    spline_power(pw, rc.w);
-    spline_power(pz, rc.z);
-    const double inv = 1.0 / nsamp;
+    // in the ray's frame (e1, e2, d) the centreline's offset (u, w) from the
+    // ray and its position z along it are cubics in s, in power form from the
+    // projected control points, so a sample costs three Horner steps per
+    // coordinate and r^2 = u^2 + w^2 has no cancellation
+    spline_power(pu, v->rc.u);
+    spline_power(pw, v->rc.w);
+    spline_power(pz, v->rc.z);
+    v->R2 = R * R;
+    v->inv = 1.0 / nsamp;
+    return true;
+}
+
+// The smallest entry T(s_i) > t_min over the samples i = i0, i0 + di, ... <=
+// nsamp and its index (+inf, -1: none).
+__device__ inline void span_sample(const SpanView& v, double t_min, int i0, int di, int nsamp, double* t_out,
+                                   int* i_out)
+{
     double bt = INFINITY;
     int bi = -1;
-    for (int i = 0; i <= nsamp; ++i) {
-        const double t = entry_at(rc, R, i * inv, t_min);
-        if (t < bt) {
-            bt = t;
-            bi = i;
-        }
+    for (int i = i0; i <= nsamp; i += di) {
+        const double s = i * v.inv, u = horner3(v.rc.u, s), w = horner3(v.rc.w, s);
+        const double q2 = fma(-u, u, fma(-w, w, v.R2));
+        // the root from the hardware estimate and one correction, within a
+        // few ulps; a ball that misses the ray (q2 <= 0) makes it a NaN, which
+        // no comparison takes
+        const double y = bysdf::rsq_estimate(q2), q = q2 * y;
+        const double t = horner3(v.rc.z, s) - fma(q, fma(-q, 0.5 * y, 0.5), q);
+        const bool in = t > t_min && t < bt;
+        bt = in ? t : bt;
+        bi = in ? i : bi;
     }
-    if (bi < 0 || bt > t_lim) return false;
     *t_out = bt;
     *i_out = bi;
-    return true;
+}
+
+// The entry at sample bi of a span whose ball there meets the ray.  Where two
+// spans join, both hold the same entry up to rounding, and the last bits of
+// this value and of the refined one say which of them is reported; every
+// product is fused as written, so that all kernels report the same span.
+__device__ inline double sample_entry(const SpanGeo& g, D3 d, D3 e1, D3 e2, int nsamp, int bi)
+{
+#pragma clang fp contract(off)
+    auto across = [](D3 a, D3 b) { return fma(a.z, b.z, fma(a.x, b.x, a.y * b.y)); };
+    auto power = [](const double* c, double s) {
+        const double a0 = (fma(4.0, c[1], c[0]) + c[2]) * (1.0 / 6.0), a1 = (c[2] - c[0]) * 0.5;
+        const double a2 = (fma(-2.0, c[1], c[0]) + c[2]) * 0.5;
+        const double a3 = fma(3.0, c[1] - c[2], c[3] - c[0]) * (1.0 / 6.0);
+        return fma(fma(fma(a3, s, a2), s, a1), s, a0);
+    };
+    double pu[4], pw[4], pz[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        pu[k] = across(g.c[k], e1);
+        pw[k] = across(g.c[k], e2);
+        pz[k] = k & 1 ? across(g.c[k], d) : fma(g.c[k].z, d.z, fma(g.c[k].y, d.y, g.c[k].x * d.x));
+    }
+    const double s = bi * (1.0 / nsamp), u = power(pu, s), w = power(pw, s);
+    const double q2 = g.R * g.R - fma(u, u, w * w);
+    return power(pz, s) - bysdf::sqrt_(q2);
 }
 
 // Minimum of T in the bracket of sample bi (best sampled value bt):
@@ -251,12 +298,16 @@ __host__ __device__ inline void span_refine(const SpanGeo& g, D3 d, D3 e1, D3 e2
 {
     RayCubic rc;
     {
+        // Newton's last steps move s by far more than an ulp when a product
+        // rounds differently, so the order of these sums is fixed here and
+        // not left to how the compiler fuses them in each place
+        auto proj = [](D3 a, D3 b) { return fma(a.z, b.z, fma(a.y, b.y, a.x * b.x)); };
         double pu[4], pw[4], pz[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            pu[k] = dot(g.c[k], e1);
-            pw[k] = dot(g.c[k], e2);
-            pz[k] = dot(g.c[k], d);
+            pu[k] = proj(g.c[k], e1);
+            pw[k] = proj(g.c[k], e2);
+            pz[k] = proj(g.c[k], d);
         }
         spline_power(pu, rc.u);
         spline_power(pw, rc.w);
@@ -419,28 +470,77 @@ __host__ __device__ inline int leaf_code(int first, int count) { return -((first
 // end of a traversal: below every leaf code of a scene of fewer than 2^29 spans
 constexpr int kTraceDone = INT32_MIN;
 
-// Whether the predicate holds on any active lane of the wavefront (on the
-// host, a single lane: the predicate itself).
-__host__ __device__ inline bool wave_any(bool p)
+// ---------------------------------------------------------------- four lanes per ray
+// The traversal kernels give each ray the four lanes of a quad (16 rays per
+// wavefront).  A lane tests one child of a 4-wide node and scans one span of
+// a leaf (leaves hold up to four), so a node or leaf step of a ray takes a
+// quarter of the instructions in a row that one lane would need, and a
+// wavefront waits for the longest of 16 rays instead of 64.  Every lane of a
+// quad holds the ray's state and takes the same branches; the exchanges
+// below are register moves within the quad (DPP), and the ray's stack sits in
+// LDS, one entry per ray and level.
+constexpr int kQuad = 4;
+
+__device__ inline int quad_lane() { return __lane_id() & (kQuad - 1); }
+template <int CTRL> __device__ inline int quad_perm(int x)
 {
-#if defined(__HIP_DEVICE_COMPILE__)
-    return __any((int)p) != 0;
-#else
-    return p;
-#endif
+    return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
+}
+// the value of the lane whose index in the quad differs by the given bits
+__device__ inline int quad_xor1(int x) { return quad_perm<0xb1>(x); }
+__device__ inline int quad_xor2(int x) { return quad_perm<0x4e>(x); }
+__device__ inline float quad_xor1(float x) { return __int_as_float(quad_xor1(__float_as_int(x))); }
+__device__ inline float quad_xor2(float x) { return __int_as_float(quad_xor2(__float_as_int(x))); }
+__device__ inline double quad_xor1(double x)
+{
+    return __hiloint2double(quad_xor1(__double2hiint(x)), quad_xor1(__double2loint(x)));
+}
+__device__ inline double quad_xor2(double x)
+{
+    return __hiloint2double(quad_xor2(__double2hiint(x)), quad_xor2(__double2loint(x)));
+}
+__device__ inline int quad_or(int x)
+{
+    x |= quad_xor1(x);
+    return x | quad_xor2(x);
+}
+__device__ inline double quad_min(double x)
+{
+    x = fmin(x, quad_xor1(x));
+    return fmin(x, quad_xor2(x));
+}
+// the predicate of the quad's four lanes as bits 0..3
+__device__ inline int quad_bits(bool p)
+{
+    return (int)((__ballot(p) >> (__lane_id() & ~(kQuad - 1))) & 0xf);
+}
+// Orders the LDS accesses of a wavefront's lanes to each other's slots: LDS
+// serves a wavefront's operations in issue order, so this emits nothing and
+// only keeps the compiler from moving accesses across it.
+__device__ inline void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// box of child c (0..3) of a wide node
-__host__ __device__ inline float comp4(const float4& v, int c)
+// child of the calling lane in a wide node
+struct ChildBox {
+    float3 lo, hi;
+    int code, yarn;
+};
+__device__ inline ChildBox load_child(const WNode* node, int code)
 {
-    return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
-}
-__host__ __device__ inline int comp4i(const int4& v, int c)
-{
-    return c == 0 ? v.x : (c == 1 ? v.y : (c == 2 ? v.z : v.w));
+    const WChild w = node[code].child[quad_lane()];
+    ChildBox b;
+    b.lo = make_float3(w.lo_code.x, w.lo_code.y, w.lo_code.z);
+    b.code = __float_as_int(w.lo_code.w);
+    b.hi = make_float3(w.hi_yarn.x, w.hi_yarn.y, w.hi_yarn.z);
+    b.yarn = __float_as_int(w.hi_yarn.w);
+    return b;
 }
 
-__host__ __device__ inline bool box_ray(float3 lo, float3 hi, float3 o, float3 inv, float t0, float t1, float* tn)
+__device__ inline bool box_ray(float3 lo, float3 hi, float3 o, float3 inv, float t0, float t1, float* tn)
 {
     float ax = (lo.x - o.x) * inv.x, bx = (hi.x - o.x) * inv.x;
     float ay = (lo.y - o.y) * inv.y, by = (hi.y - o.y) * inv.y;
@@ -453,63 +553,240 @@ __host__ __device__ inline bool box_ray(float3 lo, float3 hi, float3 o, float3 i
     return tmin <= tmax;
 }
 
-__host__ __device__ inline bool box_point(float3 lo, float3 hi, float3 p)
+__device__ inline bool box_point(float3 lo, float3 hi, float3 p)
 {
     return p.x >= lo.x && p.x <= hi.x && p.y >= lo.y && p.y <= hi.y && p.z >= lo.z && p.z <= hi.z;
 }
 
+// Yarns a ray skips: those whose tube holds its origin (at most
+// kMaxExcluded) and the yarn it leaves.  Unused entries are -1.
+struct Excluded {
+    int yarn[kMaxExcluded + 1];
+    int n;
+    __device__ bool has(int y) const
+    {
+        bool h = false;
+#pragma unroll
+        for (int k = 0; k <= kMaxExcluded; ++k) h |= yarn[k] == y;
+        return h;
+    }
+    __device__ void add(int y)
+    {
+#pragma unroll
+        for (int k = 0; k <= kMaxExcluded; ++k) yarn[k] = k == n ? y : yarn[k];
+        ++n;
+    }
+};
+
 // Yarns whose tube holds the origin (distance to the centreline below
-// R (1 - 1e-3)).  Point query through the BVH; stack at stk[k * stride].
-// Yarn `skip` (-1: none) is left out of the query and comes first in ex:
-// a ray leaving a yarn skips that yarn whatever its origin.
-__host__ __device__ inline int excluded_yarns(const SceneView& S, D3 o, int* stk, int stride, int* ex,
-                                              int skip = -1)
+// R (1 - 1e-3)).  Point query through the BVH, a quad per origin; the ray's
+// stack at stk[k * stride].  Yarn `skip` (-1: none) is left out of the query
+// and comes first: a ray leaving a yarn skips that yarn whatever its origin.
+__device__ inline Excluded excluded_yarns(const SceneView& S, D3 o, int* stk, int stride, int skip)
 {
-    float3 of = make_float3((float)o.x, (float)o.y, (float)o.z);
-    int nex = 0, sp = 0, code = 0;
-    if (skip >= 0) ex[nex++] = skip;
+    const float3 of = make_float3((float)o.x, (float)o.y, (float)o.z);
+    // the float origin may sit a rounding step outside a box that holds the
+    // double origin: grow the test box by a relative ulp
+    const float3 e = make_float3(fabsf(of.x) * 2.4e-7f + 1e-30f, fabsf(of.y) * 2.4e-7f + 1e-30f,
+                                 fabsf(of.z) * 2.4e-7f + 1e-30f);
+    const int me = quad_lane();
+    Excluded ex;
+#pragma unroll
+    for (int k = 0; k <= kMaxExcluded; ++k) ex.yarn[k] = -1;
+    ex.n = 0;
+    if (skip >= 0) ex.add(skip);
+    const int full = kMaxExcluded + (skip >= 0 ? 1 : 0);
+    int sp = 0, code = 0;
     while (true) {
         if (code >= 0) {
-            const WNode n = S.node[code];
-            // the float origin may sit a rounding step outside a box that
-            // holds the double origin: grow the test box by a relative ulp
-            float3 e = make_float3(fabsf(of.x) * 2.4e-7f + 1e-30f, fabsf(of.y) * 2.4e-7f + 1e-30f,
-                                   fabsf(of.z) * 2.4e-7f + 1e-30f);
-            int next = 0, nh = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float3 lo = make_float3(comp4(n.lox, c) - e.x, comp4(n.loy, c) - e.y, comp4(n.loz, c) - e.z);
-                float3 hi = make_float3(comp4(n.hix, c) + e.x, comp4(n.hiy, c) + e.y, comp4(n.hiz, c) + e.z);
-                if (box_point(lo, hi, of)) {
-                    // the first hit child is visited next, the others pushed
-                    if (nh > 0) stk[sp++ * stride] = next;
-                    next = comp4i(n.code, c);
-                    ++nh;
-                }
-            }
-            if (nh > 0) {
-                code = next;
+            const ChildBox b = load_child(S.node, code);
+            const float3 lo = make_float3(b.lo.x - e.x, b.lo.y - e.y, b.lo.z - e.z);
+            const float3 hi = make_float3(b.hi.x + e.x, b.hi.y + e.y, b.hi.z + e.z);
+            const int m = quad_bits(box_point(lo, hi, of) && !(skip >= 0 && b.yarn == skip));
+            if (m) {
+                // the last hit child is visited next, the others pushed
+                const bool mine = (m >> me) & 1, last = mine && (m >> (me + 1)) == 0;
+                if (mine && !last) stk[(sp + __popc(m & ((1 << me) - 1))) * stride] = b.code;
+                wave_lds_order();
+                sp += __popc(m) - 1;
+                code = quad_or(last ? b.code : 0);
                 continue;
             }
         } else {
             int first, count;
             decode_leaf(code, &first, &count);
-            for (int k = 0; k < count; ++k) {
-                SpanRec r = S.span[first + k];
-                bool seen = false;
-                for (int j = 0; j < nex; ++j) seen |= ex[j] == r.yarn;
-                if (seen || nex >= kMaxExcluded + (skip >= 0 ? 1 : 0)) continue;
-                SpanGeo g;
-                load_span(S, r, o, &g);
-                double lim = g.R * (1.0 - kExcludeFrac);
-                if (span_far(g, lim)) continue;
-                if (span_within(g, r.info & 0xffff, lim)) ex[nex++] = r.yarn;
+            bool in = false;
+            int y = -1;
+            if (me < count) {
+                const SpanRec r = S.span[first + me];
+                y = r.yarn;
+                if (!ex.has(y) && ex.n < full) {
+                    SpanGeo g;
+                    load_span(S, r, o, &g);
+                    const double lim = g.R * (1.0 - kExcludeFrac);
+                    in = !span_far(g, lim) && span_within(g, r.info & 0xffff, lim);
+                }
+            }
+            const int m = quad_bits(in);
+            if (m) {
+                // the leaf's spans in order, each yarn once
+                const int ys[kQuad] = {quad_perm<0x00>(y), quad_perm<0x55>(y), quad_perm<0xaa>(y), quad_perm<0xff>(y)};
+#pragma unroll
+                for (int k = 0; k < kQuad; ++k)
+                    if (((m >> k) & 1) && !ex.has(ys[k]) && ex.n < full) ex.add(ys[k]);
             }
         }
         if (sp == 0) break;
         code = stk[--sp * stride];
     }
-    return nex;
+    return ex;
+}
+
+// ---------------------------------------------------------------- rays of a wavefront
+// A wavefront traces the rays its lanes hold (one per lane, up to 32).  The
+// search works on 16 at a time, a quad each, with the ray in LDS; the spans
+// it finds go to a list, are refined one per lane whatever rays they belong
+// to, and each ray's closest entry returns to its lane, which forms the hit
+// with the other lanes.  So the refinement and everything after it run on
+// full wavefronts, once per ray instead of once per lane of its quad, and
+// the traversal keeps its registers for the span scans.
+//
+// Candidates for refinement are the spans whose best sample lies within
+// kCandMargin R of the ray's best sample.  A minimum between samples
+// undershoots its bracket's best sample by far less than that unless the
+// ray only grazes the tube (samples are at most 0.05 R apart along the
+// curve), so the true first entry is among them.
+constexpr double kCandMargin = 0.1;
+
+struct Candidate {
+    double t;  // best sampled entry
+    int span;
+    unsigned tag;  // index of the sample (16 bits), lane of the ray (6), number in the search (10, saturated)
+};
+constexpr unsigned kLastNumber = 0x3ff;
+// a double's bits in an order-preserving unsigned form, and back
+__device__ inline unsigned long long ordered_bits(double x)
+{
+    const long long b = __double_as_longlong(x);
+    return (unsigned long long)b ^ ((unsigned long long)(b >> 63) | 0x8000000000000000ull);
+}
+__device__ inline double from_ordered(unsigned long long k)
+{
+    const unsigned long long b = (k >> 63) ? k ^ 0x8000000000000000ull : ~k;
+    return __longlong_as_double((long long)b);
+}
+
+constexpr int kStragglers = 2 * kQuad;  // lanes still at nodes when leaves are scanned
+constexpr int kRays = 32;     // rays of a wavefront at most
+// spans whose samples a wavefront shares at a time: 8, 12 and 32 take 1.32,
+// 1.28 and 1.27 ms on the primary rays, 16 takes 1.23 (more rounds below,
+// more LDS and fewer wavefronts above)
+constexpr int kShared = 16;
+struct WaveRays {
+    double dx[kRays], dy[kRays], dz[kRays], e1x[kRays], e1y[kRays], e1z[kRays], e2x[kRays], e2y[kRays], e2z[kRays], t_max[kRays];
+    unsigned long long tb[kRays];             // smallest sampled entry so far, or t_max, as ordered bits
+    unsigned long long key[kRays], key2[kRays];  // the closest entry and its sample, likewise
+    double s[kRays];
+    float ox[kRays], oy[kRays], oz[kRays];
+    unsigned long long pick[kRays];  // its number in the search << 32 | span
+    int skip[kRays], list[kRays];
+    int excl[kMaxExcluded + 1][kRays], n_excl[kRays];  // the ray's Excluded
+    int give[kWaveRays];
+    Candidate cand[128];
+    // spans whose samples are shared among lanes: views, samples, results
+    SpanView view[kShared];
+    unsigned long long best[kShared];
+    int samples[kShared], best_at[kShared];
+    __device__ D3 origin(int l) const { return d3(ox[l], oy[l], oz[l]); }
+    __device__ D3 dir(int l) const { return d3(dx[l], dy[l], dz[l]); }
+    // two unit vectors across the ray
+    __device__ D3 e1(int l) const { return d3(e1x[l], e1y[l], e1z[l]); }
+    __device__ D3 e2(int l) const { return d3(e2x[l], e2y[l], e2z[l]); }
+    // lane l's ray; the origin's components are single-precision values
+    __device__ void set(int l, D3 o, D3 d, double tmax, int skip_yarn)
+    {
+        move(l, o, tmax, skip_yarn);
+        dx[l] = d.x;
+        dy[l] = d.y;
+        dz[l] = d.z;
+        const D3 a = fabs(d.x) < 0.9 ? d3(1, 0, 0) : d3(0, 1, 0);
+        const D3 e1 = unit(cross(d, a)), e2 = cross(d, e1);
+        e1x[l] = e1.x;
+        e1y[l] = e1.y;
+        e1z[l] = e1.z;
+        e2x[l] = e2.x;
+        e2y[l] = e2.y;
+        e2z[l] = e2.z;
+    }
+    // the same ray from another point
+    __device__ void move(int l, D3 o, double tmax, int skip_yarn)
+    {
+        ox[l] = (float)o.x;
+        oy[l] = (float)o.y;
+        oz[l] = (float)o.z;
+        t_max[l] = tmax;
+        tb[l] = ordered_bits(tmax);
+        skip[l] = skip_yarn;
+    }
+};
+
+// Refines the listed candidates [first, first + n), n <= 64, one per lane, and
+// folds them into their rays' closest entries (equal entries, where two spans
+// join: the smaller sample, then the span met first).  A candidate beyond its ray's margin by now is
+// dropped.  Called by the whole wavefront.
+__device__ inline void refine_listed(const SceneView& S, WaveRays& W, int first, int n, double t_min)
+{
+    const int lane = __lane_id();
+    bool ok = lane < n;
+    int ray = 0;
+    double s = 0.0;
+    unsigned long long key = ~0ull, key2 = ~0ull, pick = ~0ull;
+    if (ok) {
+        const Candidate c = W.cand[first + lane];
+        ray = (c.tag >> 16) & 63;
+        pick = (unsigned long long)(c.tag >> 22) << 32 | (unsigned)c.span;
+        const SpanRec r = S.span[c.span];
+        const int nsamp = r.info & 0xffff, at = c.tag & 0xffff;
+        double bt = 0.0;
+        {
+            SpanGeo g;
+            load_span(S, r, W.origin(ray), &g);
+            ok = c.t <= from_ordered(W.tb[ray]) + kCandMargin * g.R;
+            if (ok) bt = sample_entry(g, W.dir(ray), W.e1(ray), W.e2(ray), nsamp, at);
+        }
+        // the span and the ray are read again rather than kept in registers
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (ok) {
+            SpanGeo g;
+            load_span(S, r, W.origin(ray), &g);
+            double t;
+            span_refine(g, W.dir(ray), W.e1(ray), W.e2(ray), t_min, nsamp, at, bt, &t, &s);
+            ok = t <= W.t_max[ray];
+            key = ordered_bits(t);
+            key2 = ordered_bits(bt);
+        }
+    }
+    const unsigned long long before = ok ? W.key[ray] : 0ull;
+    wave_lds_order();
+    if (ok) atomicMin(&W.key[ray], key);
+    wave_lds_order();
+    bool win = ok && W.key[ray] == key;
+    if (win && key < before) {
+        W.key2[ray] = ~0ull;
+        W.pick[ray] = ~0ull;
+    }
+    wave_lds_order();
+    const unsigned long long before2 = win ? W.key2[ray] : 0ull;
+    wave_lds_order();
+    if (win) atomicMin(&W.key2[ray], key2);
+    wave_lds_order();
+    win = win && W.key2[ray] == key2;
+    if (win && key2 < before2) W.pick[ray] = ~0ull;
+    wave_lds_order();
+    if (win) atomicMin(&W.pick[ray], pick);
+    wave_lds_order();
+    if (win && W.pick[ray] == pick) W.s[ray] = s;
+    wave_lds_order();
 }
 
 struct RayHit {
@@ -517,162 +794,242 @@ struct RayHit {
     int span;  // leaf-order span index, -1 for a miss
 };
 
-// Candidates kept for refinement: spans whose best sample lies within
-// kCandMargin R of the best sample so far.  A minimum between samples
-// undershoots its bracket's best sample by far less than that unless the
-// ray only grazes the tube (samples are at most 0.05 R apart along the
-// curve), so the true first entry is among them.
-constexpr int kCand = 6;
-constexpr double kCandMargin = 0.1;
-
-// Closest entering hit with t_min < t <= t_max.  Traversal ranks spans by
-// their sampled entries (an upper bound of the true entry, so it is safe
-// for culling); only the candidates are refined, once, at the end.
-__host__ __device__ inline RayHit closest_hit(const SceneView& S, D3 o, D3 d, double t_min, double t_max,
-                                              const int* ex, int nex, int* stk, int stride)
+// Closest entering hits with t_min < t <= t_max of the wavefront's rays: lane
+// l's ray if live, left in slot l of W by the caller.  n_ex returns how many
+// yarns hold the ray's origin.  Called by the whole wavefront; stk: its
+// quads' stacks, entry k of quad q at stk[16 k + q].
+//
+// The quads take 16 rays; a quad that is done takes the farthest pending
+// subtree of a quad that still works, so that one long ray (a path that skims
+// the cloth visits thousands of nodes) has up to 64 lanes, and when all are
+// done they take the next 16 (a quad that took its next ray by itself would
+// make the point queries of new rays run a few at a time: 1.32 against 1.20 ms
+// on the weave's primary rays).  Spans are ranked by their
+// sampled entries (an upper bound of the true entry, so it is safe for
+// culling), and a ray's bound is shared by every quad working on it.
+//
+// The traversal is bound by VALU issue where the chip is full and by the
+// dependent loads of the longest ray where it is not.  Against one lane per
+// ray (a fan of 64 rays waits for its longest; 17 samples of a span in a row
+// for any lane that needs them) a 320 x 180 preview at 4 spp and depth 4
+// takes 2.24 instead of 4.3 ms and a 48 x 48 crop with its gradient at 16 spp
+// 1.00 instead of 3.25 ms; the weave's 2.07 M primary rays take 1.21 instead
+// of 1.24 ms (fewer lanes idle, but rays are set up and finished 32 at a time).
+__device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, bool live, double t_min, int& n_ex)
 {
-    float3 of = make_float3((float)o.x, (float)o.y, (float)o.z);
-    float3 inv = make_float3(1.0f / (fabs(d.x) > 1e-30 ? (float)d.x : 1e-30f),
-                             1.0f / (fabs(d.y) > 1e-30 ? (float)d.y : 1e-30f),
-                             1.0f / (fabs(d.z) > 1e-30 ? (float)d.z : 1e-30f));
-    // the float origin is within a relative ulp of the double one: widen
-    // the slab interval by that much along the ray
-    float slack = 2.4e-7f * (fabsf(of.x) + fabsf(of.y) + fabsf(of.z)) + 1e-30f;
-    // basis of the plane across the ray (for the span hull test)
-    D3 a = fabs(d.x) < 0.9 ? d3(1, 0, 0) : d3(0, 1, 0);
-    D3 e1 = unit(cross(d, a)), e2 = cross(d, e1);
-    // candidates sorted by sampled entry (static indices: registers)
-    double ct[kCand];
-    int cs[kCand], ci[kCand];
-#pragma unroll
-    for (int k = 0; k < kCand; ++k) {
-        ct[k] = INFINITY;
-        cs[k] = -1;
-        ci[k] = 0;
+    const int lane = __lane_id(), quad = lane / kQuad, me = quad_lane();
+    const unsigned long long kLeaders = 0x1111111111111111ull;
+    const unsigned long long below = (1ull << (lane & ~(kQuad - 1))) - 1ull;  // lanes of lower quads
+    int* my = stk + quad;
+    const unsigned long long m = __ballot(live);
+    const int n = __popcll(m), slot = __popcll(m & ((1ull << lane) - 1ull));
+    if (live) {
+        W.list[slot] = lane;
+        W.key[lane] = W.key2[lane] = W.pick[lane] = ~0ull;
     }
-    double tb = t_max;  // best sampled entry (bounds the true first entry)
-    int sp = 0, code = 0;
-    float t0 = (float)t_min - slack;
-    // Two inner loops (the while-while form of Aila and Laine, HPG 2009,
-    // with their postponed leaves): a lane that reaches a leaf holds it and
-    // goes on through nodes until every lane of the wavefront holds a leaf
-    // or is done; then the held leaves are scanned one span per step, with
-    // the leaves met meanwhile.  The expensive span scans so run with most
-    // lanes active.  A lane may visit nodes before scanning a leaf it holds,
-    // with the larger bound tb of that moment: that costs only pruning.  A
-    // span that survives the final filter of the candidates (sampled entry
-    // within kCandMargin R of the final tb) passes the scan limit whenever
-    // it is scanned, and the candidate list keeps the smallest entries, so
-    // the refined candidates, and the hit, do not depend on the order.
+    wave_lds_order();
+    int listed = 0, next = 0;
+    unsigned number = 0;  // candidates met so far
+    int ray = 0, sp = 0, bottom = 0, code = kTraceDone;
     int leaf = 0;  // the held leaf's code, 0 for none
-    while (code != kTraceDone || leaf != 0) {
-        while (code >= 0) {
-            const float t1 = (float)tb + slack;
-            const WNode n = S.node[code];
-            float tn[4];
-            int cc[4];
+    float3 of = make_float3(0.f, 0.f, 0.f), inv = of;
+    float slack = 0.f;
+    int leaving = -1, n_excl = 0;  // the ray's skip and its number of excluded yarns
+    while (true) {
+        const bool idle = code == kTraceDone && leaf == 0;
+        const unsigned long long mi = __ballot(idle) & kLeaders;
+        const int n_idle = __popcll(mi);
+        bool take = false;
+        if (listed >= 64 || (listed > 0 && n_idle == kWaveRays && next >= n)) {
+            const int k = min(listed, 64);
+            listed -= k;
+            refine_listed(S, W, listed, k, t_min);
+            continue;
+        }
+        if (n_idle == kWaveRays) {
+            if (next >= n) break;
+            const int k = next + quad;
+            take = k < n;
+            if (take) {
+                ray = W.list[k];
+                const int skip = W.skip[ray];
+                const Excluded ex = excluded_yarns(S, W.origin(ray), my, kWaveRays, skip);
+                if (me == 0) {
+                    W.n_excl[ray] = ex.n;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float3 lo = make_float3(comp4(n.lox, c), comp4(n.loy, c), comp4(n.loz, c));
-                float3 hi = make_float3(comp4(n.hix, c), comp4(n.hiy, c), comp4(n.hiz, c));
-                float t;
-                tn[c] = box_ray(lo, hi, of, inv, t0, t1, &t) ? t : INFINITY;
-                cc[c] = comp4i(n.code, c);
+                    for (int e = 0; e <= kMaxExcluded; ++e) W.excl[e][ray] = ex.yarn[e];
+                }
+                code = 0;
             }
-            // hit children near first (a sorting network; misses sort last)
-#define YARN_CSWAP(a, b)                                      \
-    do {                                                      \
-        const bool sw_ = tn[b] < tn[a];                       \
-        const float ta_ = tn[a];                              \
-        const int ca_ = cc[a];                                \
-        tn[a] = sw_ ? tn[b] : tn[a];                          \
-        tn[b] = sw_ ? ta_ : tn[b];                            \
-        cc[a] = sw_ ? cc[b] : cc[a];                          \
-        cc[b] = sw_ ? ca_ : cc[b];                            \
-    } while (0)
-            YARN_CSWAP(0, 1);
-            YARN_CSWAP(2, 3);
-            YARN_CSWAP(0, 2);
-            YARN_CSWAP(1, 3);
-            YARN_CSWAP(1, 2);
-#undef YARN_CSWAP
-            if (tn[0] < INFINITY) {
+            next += kWaveRays;
+            wave_lds_order();
+        } else if (n_idle > 0) {
+            const bool gives = !idle && sp > bottom;
+            const unsigned long long mg = __ballot(gives) & kLeaders;
+            if (mg) {
+                const int rank = __popcll((idle ? mi : mg) & below);
+                if (gives && me == 0) W.give[rank] = quad;
+                wave_lds_order();
+                take = idle && rank < __popcll(mg);
+                const int from = take ? W.give[rank] : quad;
+                const int fray = __shfl(ray, from * kQuad), fbottom = __shfl(bottom, from * kQuad);
+                if (take) {
+                    ray = fray;
+                    code = stk[fbottom * kWaveRays + from];
+                }
+                if (gives && rank < n_idle) ++bottom;
+                wave_lds_order();
+            }
+        }
+        if (take) {
+            const D3 d = W.dir(ray);
+            of = make_float3(W.ox[ray], W.oy[ray], W.oz[ray]);
+            inv = make_float3(1.0f / (fabs(d.x) > 1e-30 ? (float)d.x : 1e-30f),
+                              1.0f / (fabs(d.y) > 1e-30 ? (float)d.y : 1e-30f),
+                              1.0f / (fabs(d.z) > 1e-30 ? (float)d.z : 1e-30f));
+            // widen the slab interval by a relative ulp of the origin along the ray
+            slack = 2.4e-7f * (fabsf(of.x) + fabsf(of.y) + fabsf(of.z)) + 1e-30f;
+            leaving = W.skip[ray];
+            n_excl = W.n_excl[ray];
+            sp = bottom = 0;
+            if (code < 0) {
+                leaf = code;
+                code = kTraceDone;
+            }
+        }
+        // Two inner loops (the while-while form of Aila and Laine, HPG 2009,
+        // with their postponed leaves): a ray that reaches a leaf holds it
+        // and goes on through nodes until all but two quads hold a leaf or are
+        // done (1.200 ms on the primary rays; none 1.225, four 1.212);
+        // then the held leaves are scanned, one span per lane.  A quad may
+        // visit nodes before scanning a leaf it holds, with the larger bound
+        // of that moment, and the spans of a leaf are scanned with the bound
+        // from before it: that costs only pruning.  A span that survives the
+        // final filter of the candidates (sampled entry within kCandMargin R
+        // of the ray's smallest) passes the scan limit whenever it is
+        // scanned, so the hit does not depend on the order.
+        double tb = from_ordered(W.tb[ray]);
+        const float t0 = (float)t_min - slack, t1 = (float)tb + slack;
+        while (code >= 0) {
+            const ChildBox b = load_child(S.node, code);
+            float tn;
+            // an unused slot's box lies at infinity, which t1 may equal
+            const bool hit = box_ray(b.lo, b.hi, of, inv, t0, t1, &tn) && tn < INFINITY &&
+                             !(leaving >= 0 && b.yarn == leaving);
+            if (!hit) tn = INFINITY;
+            // the rank of this lane's child, near first; ties in lane order
+            const float n1 = quad_xor1(tn), n2 = quad_xor2(tn), n3 = quad_xor2(n1);
+            const int rank = (n1 < tn || (n1 == tn && (me & 1))) + (n2 < tn || (n2 == tn && (me & 2))) +
+                             (n3 < tn || (n3 == tn && (me & 2)));
+            const int nh = __popc(quad_bits(hit));
+            if (nh > 0) {
                 // push the farther hits, farthest first
-                if (tn[3] < INFINITY) stk[sp++ * stride] = cc[3];
-                if (tn[2] < INFINITY) stk[sp++ * stride] = cc[2];
-                if (tn[1] < INFINITY) stk[sp++ * stride] = cc[1];
-                code = cc[0];
+                if (hit && rank > 0) my[(sp + nh - 1 - rank) * kWaveRays] = b.code;
+                wave_lds_order();
+                sp += nh - 1;
+                code = quad_or(rank == 0 ? b.code : 0);
             } else {
-                code = sp > 0 ? stk[--sp * stride] : kTraceDone;
+                code = sp > bottom ? my[--sp * kWaveRays] : kTraceDone;
             }
             if (leaf == 0 && code < 0 && code != kTraceDone) {
                 leaf = code;
-                code = sp > 0 ? stk[--sp * stride] : kTraceDone;
+                code = sp > bottom ? my[--sp * kWaveRays] : kTraceDone;
             }
-            if (!wave_any(leaf == 0 && code != kTraceDone)) break;
+            if (__popcll(__ballot(leaf == 0 && code != kTraceDone)) <= kStragglers) break;
         }
-        while (leaf != 0) {
+        double t = INFINITY, lim = 0.0;
+        int bi = -1, span = -1, nsamp = 0;
+        SpanView v;
+        bool sample = false;
+        if (leaf != 0) {
             int first, count;
             decode_leaf(leaf, &first, &count);
-            SpanRec r = S.span[first];
-            bool skip = false;
-            for (int j = 0; j < nex; ++j) skip |= ex[j] == r.yarn;
-            if (!skip) {
-                SpanGeo g;
-                load_span(S, r, o, &g);
-                double t;
-                int bi;
-                double lim = fmin(t_max, tb + kCandMargin * g.R);
-                if (span_scan(g, d, e1, e2, t_min, lim, r.info & 0xffff, &t, &bi)) {
-                    tb = fmin(tb, t);
-                    double nt = t;
-                    int nsp = first, nbi = bi;
-#pragma unroll
-                    for (int q = 0; q < kCand; ++q) {
-                        if (nt < ct[q]) {
-                            double tt = ct[q];
-                            int ts = cs[q], tq = ci[q];
-                            ct[q] = nt;
-                            cs[q] = nsp;
-                            ci[q] = nbi;
-                            nt = tt;
-                            nsp = ts;
-                            nbi = tq;
-                        }
-                    }
+            if (me < count) {
+                span = first + me;
+                const SpanRec r = S.span[span];
+                bool skip = false;
+                for (int e = 0; e < n_excl; ++e) skip |= W.excl[e][ray] == r.yarn;
+                if (!skip) {
+                    SpanGeo g;
+                    load_span(S, r, d3(of.x, of.y, of.z), &g);
+                    lim = fmin(W.t_max[ray], tb + kCandMargin * g.R);
+                    nsamp = r.info & 0xffff;
+                    sample = span_view(g, W.dir(ray), W.e1(ray), W.e2(ray), t_min, lim, nsamp, &v);
                 }
             }
-            // the leaf's next span, else a leaf met meanwhile (and the next
-            // entry of the stack behind it)
-            if (count > 1) {
-                leaf = leaf_code(first + 1, count - 1);
-            } else if (code < 0 && code != kTraceDone) {
+            leaf = 0;
+            if (code < 0 && code != kTraceDone) {
+                // a leaf met meanwhile
                 leaf = code;
-                code = sp > 0 ? stk[--sp * stride] : kTraceDone;
-            } else {
-                leaf = 0;
+                code = sp > bottom ? my[--sp * kWaveRays] : kTraceDone;
             }
         }
-    }
-    RayHit best{t_max, 0.0, -1};
-#pragma unroll
-    for (int q = 0; q < kCand; ++q) {
-        if (cs[q] < 0) continue;
-        SpanRec r = S.span[cs[q]];
-        SpanGeo g;
-        load_span(S, r, o, &g);
-        if (ct[q] > tb + kCandMargin * g.R) continue;
-        double t, s;
-        span_refine(g, d, e1, e2, t_min, r.info & 0xffff, ci[q], ct[q], &t, &s);
-        if (t < best.t || (t == best.t && best.span < 0)) {
-            best.t = t;
-            best.s = s;
-            best.span = cs[q];
+        // The spans left to sample are few (about a third of the lanes' spans):
+        // their views go through LDS and the wavefront's 64 lanes share the
+        // samples, 4 to 32 lanes per span, which cuts the longest part of a
+        // leaf step from 17 samples in a row to 5 or fewer.
+        for (unsigned long long ms; (ms = __ballot(sample)) != 0;) {
+            const int n_s = min(__popcll(ms), kShared), at = __popcll(ms & ((1ull << lane) - 1ull));
+            const bool mine = sample && at < kShared;
+            if (mine) {
+                W.view[at] = v;
+                W.samples[at] = nsamp;
+                W.best[at] = ~0ull;
+                W.best_at[at] = INT32_MAX;
+            }
+            wave_lds_order();
+            const int sh = min(5, __clz(n_s - 1) - 26);  // log2 of the lanes per span
+            const int k = lane >> sh;
+            double st = INFINITY;
+            int si = -1;
+            if (k < n_s) {
+                const SpanView vk = W.view[k];
+                span_sample(vk, t_min, lane & ((1 << sh) - 1), 1 << sh, W.samples[k], &st, &si);
+                if (si >= 0) atomicMin(&W.best[k], ordered_bits(st));
+            }
+            wave_lds_order();
+            if (si >= 0 && W.best[k] == ordered_bits(st)) atomicMin(&W.best_at[k], si);
+            wave_lds_order();
+            if (mine) {
+                if (W.best_at[at] != INT32_MAX) {
+                    bi = W.best_at[at];
+                    t = from_ordered(W.best[at]);
+                }
+                sample = false;
+            }
+        }
+        const bool add = bi >= 0 && t <= lim;
+        const unsigned long long ma = __ballot(add);
+        if (ma) {
+            if (add) {
+                const int k = __popcll(ma & ((1ull << lane) - 1ull));
+                W.cand[listed + k] = Candidate{t, span, (unsigned)bi | (unsigned)ray << 16 |
+                                                            min(number + k, kLastNumber) << 22};
+                atomicMin(&W.tb[ray], ordered_bits(t));
+            }
+            wave_lds_order();
+            listed += __popcll(ma);
+            number += __popcll(ma);
         }
     }
-    if (!(best.t <= t_max)) best.span = -1;
-    return best;
+    RayHit h{INFINITY, 0.0, -1};
+    n_ex = 0;
+    if (live) {
+        n_ex = W.n_excl[lane] - (W.skip[lane] >= 0 ? 1 : 0);
+        if (W.pick[lane] != ~0ull) {
+            h.t = from_ordered(W.key[lane]);
+            h.s = W.s[lane];
+            h.span = (int)W.pick[lane];
+        }
+    }
+    wave_lds_order();
+    return h;
 }
+
+// Rays a wavefront takes per visit of its lanes: 32 where that leaves the
+// chip full, 16 for the short queues of late bounces and small batches,
+// whose time is the longest ray's and not the issue rate.
+__host__ __device__ inline int rays_per_wave(int64_t n) { return n >= 2 * 65536 ? kRays : kWaveRays; }
 
 // Frame, h and arc length at a hit.
 struct HitFrame {
@@ -736,54 +1093,61 @@ __host__ __device__ inline HitFrame hit_frame(const SceneView& S, int span, doub
     return h;
 }
 
-// One ray: exclusion point query, closest entering hit, hit frame, h, v.
-// stk: this lane's stack entries at stk[k * stride].
-__host__ __device__ inline void intersect_ray(const SceneView& S, int64_t i, const yarn_ray_soa& R,
-                                              double t_min, const yarn_hit_soa& H, int* stk, int stride)
+// Rays [i, i + count) by one wavefront, lane l ray i + l: exclusion point
+// query, closest entering hit, hit frame, h, v.
+__device__ inline void intersect_rays(const SceneView& S, int64_t i0, int count, const yarn_ray_soa& R, double t_min,
+                                      const yarn_hit_soa& H, WaveRays& W, int* stk)
 {
-    D3 o = d3(R.o_x[i], R.o_y[i], R.o_z[i]);
-    D3 dr = d3(R.d_x[i], R.d_y[i], R.d_z[i]);
-    double tm = R.t_max[i];
-    double l2 = dot(dr, dr);
+    const int lane = __lane_id();
+    const int64_t i = i0 + lane;
+    const bool in = lane < count;
     uint32_t flags = 0;
-    bool ok = __builtin_isfinite(o.x) && __builtin_isfinite(o.y) && __builtin_isfinite(o.z) &&
-              __builtin_isfinite(l2) && l2 > 0.0 && !__builtin_isnan(tm);
-    if (ok) {
-        D3 d = dr * (1.0 / sqrt(l2));
-        int ex[kMaxExcluded];
-        int nex = excluded_yarns(S, o, stk, stride, ex);
-        if (nex) flags |= HIT_EXCLUDED;
-        RayHit hit = closest_hit(S, o, d, t_min, tm, ex, nex, stk, stride);
-        if (hit.span >= 0) {
-            SpanRec r = S.span[hit.span];
-            HitFrame f = hit_frame(S, hit.span, hit.s);
-            D3 p = o + d * hit.t;
-            D3 q = p - f.c;
-            double qn = dot(q, f.N), qb = dot(q, f.B);
-            double wn = -dot(d, f.N), wb = -dot(d, f.B);
-            double ql = sqrt(qn * qn + qb * qb), wl = sqrt(wn * wn + wb * wb);
-            double h = (ql > 0.0 && wl > 0.0) ? (qb * wn - qn * wb) / (ql * wl) : 0.0;
-            h = fmin(1.0, fmax(-1.0, h));
-            if (((r.info >> 16) & 1) && hit.s <= 0.0) flags |= HIT_CAP;
-            if (((r.info >> 17) & 1) && hit.s >= 1.0) flags |= HIT_CAP;
-            H.t[i] = (float)hit.t;
-            H.yarn[i] = r.yarn;
-            H.seg[i] = r.seg;
-            H.s[i] = (float)hit.s;
-            H.h[i] = (float)h;
-            H.u[i] = S.yarn_phase[r.yarn];
-            H.v[i] = (float)f.v;
-            H.tan_x[i] = (float)f.T.x;
-            H.tan_y[i] = (float)f.T.y;
-            H.tan_z[i] = (float)f.T.z;
-            H.nrm_x[i] = (float)f.N.x;
-            H.nrm_y[i] = (float)f.N.y;
-            H.nrm_z[i] = (float)f.N.z;
-            H.flags[i] = flags;
-            return;
+    bool ok = false;
+    if (in) {
+        const D3 o = d3(R.o_x[i], R.o_y[i], R.o_z[i]);
+        const D3 dr = d3(R.d_x[i], R.d_y[i], R.d_z[i]);
+        const double tm = R.t_max[i];
+        const double l2 = dot(dr, dr);
+        ok = __builtin_isfinite(o.x) && __builtin_isfinite(o.y) && __builtin_isfinite(o.z) &&
+             __builtin_isfinite(l2) && l2 > 0.0 && !__builtin_isnan(tm);
+        if (ok) {
+            W.set(lane, o, dr * (1.0 / sqrt(l2)), tm, -1);
+        } else {
+            flags |= HIT_BAD_INPUT;
         }
-    } else {
-        flags |= HIT_BAD_INPUT;
+    }
+    int n_ex;
+    const RayHit hit = trace_wave(S, W, stk, ok, t_min, n_ex);
+    if (n_ex) flags |= HIT_EXCLUDED;
+    if (!in) return;
+    if (hit.span >= 0) {
+        const D3 o = W.origin(lane), d = W.dir(lane);
+        SpanRec r = S.span[hit.span];
+        HitFrame f = hit_frame(S, hit.span, hit.s);
+        D3 p = o + d * hit.t;
+        D3 q = p - f.c;
+        double qn = dot(q, f.N), qb = dot(q, f.B);
+        double wn = -dot(d, f.N), wb = -dot(d, f.B);
+        double ql = sqrt(qn * qn + qb * qb), wl = sqrt(wn * wn + wb * wb);
+        double h = (ql > 0.0 && wl > 0.0) ? (qb * wn - qn * wb) / (ql * wl) : 0.0;
+        h = fmin(1.0, fmax(-1.0, h));
+        if (((r.info >> 16) & 1) && hit.s <= 0.0) flags |= HIT_CAP;
+        if (((r.info >> 17) & 1) && hit.s >= 1.0) flags |= HIT_CAP;
+        H.t[i] = (float)hit.t;
+        H.yarn[i] = r.yarn;
+        H.seg[i] = r.seg;
+        H.s[i] = (float)hit.s;
+        H.h[i] = (float)h;
+        H.u[i] = S.yarn_phase[r.yarn];
+        H.v[i] = (float)f.v;
+        H.tan_x[i] = (float)f.T.x;
+        H.tan_y[i] = (float)f.T.y;
+        H.tan_z[i] = (float)f.T.z;
+        H.nrm_x[i] = (float)f.N.x;
+        H.nrm_y[i] = (float)f.N.y;
+        H.nrm_z[i] = (float)f.N.z;
+        H.flags[i] = flags;
+        return;
     }
     H.t[i] = INFINITY;
     H.yarn[i] = -1;
