@@ -156,7 +156,11 @@ __host__ __device__ inline void promote(const XState<double, float, MP>& a, XSta
     b.Gf = DF(a.Gf);
     b.mu_i = DF(a.mu_i);
     for (int k = 0; k < 4; ++k) b.w[k] = DF(a.w[k]);
-    b.a = DD(a.a);
+    b.g1i = DF(a.g1i);
+    b.q4 = DF(a.q4);
+    b.body = DF(a.body);
+    b.ca = DD(a.ca);
+    b.sa = DD(a.sa);
     b.rawp = DD(a.rawp);
     b.rawf = DD(a.rawf);
 }
@@ -188,6 +192,7 @@ __host__ __device__ inline Derived<DD, DF> derive_dual(const TypeRec& t, int see
     d.ax = Narrow<DF>::from(d.ax_g);
     d.ay = Narrow<DF>::from(d.ay_g);
     d.eta = DF(f.eta);
+    d.inv_eta2 = DF(f.inv_eta2);
     d.kS = DF(f.kS); d.B = DF(f.B); d.r = DF(f.r); d.sigma_t = DF(f.sigma_t);
     d.rho_p = DF(f.rho_p); d.rho_f = DF(f.rho_f); d.dP = DF(f.dP);
     for (int c = 0; c < 3; ++c) d.alb[c] = DF(f.alb[c]);

@@ -1466,6 +1466,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_BACKWARD_MIN_WAVES) void k_backward(c
                 XState<double, float, MP> Xp;
                 state_at_x(rec.d, tab, h, u, v, wi, Xp);
                 promote(Xp, X);
+                lobe_weights(P, X);  // the terms at x that depend on beta
             } else if (PASS == 2) {
                 PlyHit<double, MP> ph;
                 trace_plies(rec.d, h, u, v, wi, ph);

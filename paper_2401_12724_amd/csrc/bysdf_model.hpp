@@ -54,7 +54,7 @@ template <class G, class S> struct Derived {
     double inv_np;
     G rp, Rpc, slope, wp_turns, tnorm_inv, vply_scale, wf_turns, tan_af;
     G ax_g, ay_g, eta_g, inv_eta_g;
-    S ax, ay, eta, kS, B, r, sigma_t, rho_p, rho_f, dP;
+    S ax, ay, eta, inv_eta2, kS, B, r, sigma_t, rho_p, rho_f, dP;
     S alb[3];
     S rp_s, Rpc_s;
     // fiber migration (Sec. 3.5.2): n_mig tables switched per period of
@@ -80,10 +80,10 @@ struct TypeRec {
     uint32_t mig_seed;
     double mig_period, mig_blend, mig_spread;
     Derived<double, float> d;
-    // disk points (d1, d2) of the visible-normal samples of the K forward
-    // nodes without a lattice shift: they depend on K alone, so they are
-    // formed once at creation and read with scalar loads
-    double node_disk[2 * kMaxNodes];
+    // disk points (d1, d2, sqrt(1 - d1^2)) of the visible-normal samples of
+    // the K forward nodes without a lattice shift: they depend on K alone, so
+    // they are formed once at creation and read with scalar loads
+    double node_disk[3 * kMaxNodes];
 };
 
 // Fill the derived scalars of a record (host at creation, device when the
@@ -109,6 +109,7 @@ __host__ __device__ inline void fill_derived(TypeRec& t)
     d.ax = (float)t.beta;
     d.ay = (float)(t.beta * t.aniso);
     d.eta = (float)t.eta;
+    d.inv_eta2 = (float)(1.0 / (t.eta * t.eta));
     d.kS = t.k_spec; d.B = t.B; d.r = t.r; d.sigma_t = t.sigma_t;
     d.rho_p = t.ply_density; d.rho_f = t.fiber_density; d.dP = t.shadow_hw;
     for (int c = 0; c < 3; ++c) d.alb[c] = t.albedo[c];
@@ -137,7 +138,7 @@ template <class G2, class S2> inline Derived<G2, S2> rebind(const Derived<double
     d.tnorm_inv = G2(f.tnorm_inv); d.vply_scale = G2(f.vply_scale); d.wf_turns = G2(f.wf_turns);
     d.tan_af = G2(f.tan_af); d.ax_g = G2(f.ax_g); d.ay_g = G2(f.ay_g); d.eta_g = G2(f.eta_g);
     d.inv_eta_g = G2(f.inv_eta_g);
-    d.ax = S2(f.ax); d.ay = S2(f.ay); d.eta = S2(f.eta); d.kS = S2(f.kS); d.B = S2(f.B); d.r = S2(f.r);
+    d.ax = S2(f.ax); d.ay = S2(f.ay); d.eta = S2(f.eta); d.inv_eta2 = S2(f.inv_eta2); d.kS = S2(f.kS); d.B = S2(f.B); d.r = S2(f.r);
     d.sigma_t = S2(f.sigma_t); d.rho_p = S2(f.rho_p); d.rho_f = S2(f.rho_f); d.dP = S2(f.dP);
     for (int c = 0; c < 3; ++c) d.alb[c] = S2(f.alb[c]);
     d.rp_s = S2(f.rp_s); d.Rpc_s = S2(f.Rpc_s);
@@ -172,14 +173,15 @@ template <class S> __host__ __device__ inline S fresnel(S c, S e)
 
 // Fresnel transmittance 1 - F written without the cancellation of 1 - F
 // near total internal reflection: 1 - r^2 = 4 c e c_t / (c + e c_t)^2 per
-// polarisation.
-template <class S> __host__ __device__ inline S fresnel_T(S c, S e)
+// polarisation, the two quotients over one denominator.  ie2 = 1 / e^2.
+template <class S> __host__ __device__ inline S fresnel_T(S c, S e, S ie2)
 {
-    S s2t = (S(1) - c * c) * rcp_(e * e);
+    S s2t = (S(1) - c * c) * ie2;
     if (val(s2t) >= 1.0f) return S(0);
     S ct = sqrt_(S(1) - s2t);
     S a = c + e * ct, b = e * c + ct;
-    return S(2) * e * c * ct * (rcp_(a * a) + rcp_(b * b));
+    S a2 = a * a, b2 = b * b;
+    return S(2) * e * c * ct * (a2 + b2) * rcp_(a2 * b2);
 }
 
 template <class S> __host__ __device__ inline S ggx_D(const V3<S>& m, S ax, S ay)
@@ -210,11 +212,15 @@ template <class S> __host__ __device__ inline S ggx_D_iso(S mz, S ms2, S a)
     S t = ms2 * ia2 + mz * mz;
     return rcp_(S(float(kPi)) * a * a * t * t);
 }
+template <class S> __host__ __device__ inline S smith_G1_front(S wz, S ws2, S a)
+{
+    S a2t2 = a * a * ws2 * rcp_(wz * wz);
+    return S(2) * rcp_(S(1) + sqrt_(S(1) + a2t2));
+}
 template <class S> __host__ __device__ inline S smith_G1_iso(S wm, S wz, S ws2, S a)
 {
     if (!(val(wm) * val(wz) > 0.0f)) return S(0);
-    S a2t2 = a * a * ws2 * rcp_(wz * wz);
-    return S(2) * rcp_(S(1) + sqrt_(S(1) + a2t2));
+    return smith_G1_front(wz, ws2, a);
 }
 template <class G> __host__ __device__ inline G one_minus_sq(const G& z) { return G(1) - z * z; }
 
@@ -231,8 +237,8 @@ template <class T> __host__ __device__ inline void vndf_disk(T u1, T u2, T& d1, 
     d1 = rad * cu;
     d2 = rad * su;
 }
-// The visible normal for the disc point (d1, d2).
-template <class T> __host__ __device__ inline V3<T> sample_vndf_disk(const V3<T>& w, T ax, T ay, T d1, T d2)
+// The visible normal for the disc point (d1, d2); r1 = sqrt(1 - d1^2).
+template <class T> __host__ __device__ inline V3<T> sample_vndf_disk(const V3<T>& w, T ax, T ay, T d1, T d2, T r1)
 {
     V3<T> vh = normalize(mk3<T>(ax * w.x, ay * w.y, w.z));
     T l2 = vh.x * vh.x + vh.y * vh.y;
@@ -240,7 +246,7 @@ template <class T> __host__ __device__ inline V3<T> sample_vndf_disk(const V3<T>
                              : mk3<T>(T(1), T(0), T(0));
     V3<T> b2 = cross(vh, b1);
     T blend = T(0.5) * (T(1) + vh.z);
-    d2 = (T(1) - blend) * sqrt_(T(1) - d1 * d1) + blend * d2;
+    d2 = (T(1) - blend) * r1 + blend * d2;
     T h2 = T(1) - d1 * d1 - d2 * d2;
     T hz = val(h2) > 0.0 ? sqrt_(h2) : T(0);
     V3<T> nh = b1 * d1 + b2 * d2 + vh * hz;
@@ -251,7 +257,7 @@ template <class T> __host__ __device__ inline V3<T> sample_vndf(const V3<T>& w, 
 {
     T d1, d2;
     vndf_disk(u1, u2, d1, d2);
-    return sample_vndf_disk(w, ax, ay, d1, d2);
+    return sample_vndf_disk(w, ax, ay, d1, d2, sqrt_(T(1) - d1 * d1));
 }
 
 // Lommel-Seeliger single-scatter albedo 1/2 [1 - mu ln(1 + 1/mu)].
@@ -406,13 +412,21 @@ __host__ __device__ inline void table_at(const Tab& tab, int Nu, int base, const
 // period's table over the period's last mig_blend share.
 template <class G, class S, class Tab>
 __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Tab& tab, G cth, G sth, int k,
-                                                G n2x, G n2y, G z, G* gf_out, G* a_out)
+                                                G n2x, G n2y, G z, G* gf_out, G* cos_out,
+                                                G* sin_out)
 {
     StageMark<G> mark(kStageFrame);
-    V3<G> tp = mk3<G>(-P.slope * sth * P.tnorm_inv, P.slope * cth * P.tnorm_inv, P.tnorm_inv);
-    V3<G> n23 = mk3<G>(n2x, n2y, G(0));
-    V3<G> np = normalize(n23 - tp * dot(n23, tp));
-    G a = atan2_(cth * n2y - sth * n2x, cth * n2x + sth * n2y);
+    // sine and cosine of the angle around the ply, (cth, sth) to (n2x, n2y)
+    const G sa_ = cth * n2y - sth * n2x, ca_ = cth * n2x + sth * n2y;
+    // tp is a unit vector with the slope's share kt across the yarn, so
+    // n2.tp = kt sin a; the ply normal and bitangent follow without products
+    // of vectors
+    const G kt = P.slope * P.tnorm_inv, ks = kt * sa_;
+    V3<G> tp = mk3<G>(-kt * sth, kt * cth, P.tnorm_inv);
+    const G rn = rsqrt_(G(1) - ks * ks), rks = rn * ks, rtz = rn * P.tnorm_inv;
+    V3<G> np = mk3<G>(rn * n2x - tp.x * rks, rn * n2y - tp.y * rks, -tp.z * rks);
+    V3<G> bp = mk3<G>(-rtz * n2y, rtz * n2x, -(rn * kt) * ca_);
+    G a = atan2_(sa_, ca_);
     const G vply = z * P.vply_scale;
     G turns = a * G(kInvTwoPi) + P.wf_turns * vply;
     G dn, rh, gfv;
@@ -434,38 +448,40 @@ __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Ta
     } else {
         table_at(tab, P.Nu, 0, turns, dn, rh, gfv);
     }
-    V3<G> bp = cross(tp, np);
     G sdn, cdn;
     sincos_turns_g(dn * G(kInvTwoPi), &sdn, &cdn);
-    V3<G> npr = np * cdn + bp * sdn;
     G tfa = rh * P.tan_af;
     G ca = rsqrt_(G(1) + tfa * tfa);
     G sa = tfa * ca;
     Frame<G> fr;
     fr.t = tp * ca - bp * sa;
-    fr.n = normalize(npr - fr.t * dot(npr, fr.t));
+    // the turned normal np cos dn + bp sin dn, made orthogonal to fr.t and
+    // normalised, in the orthonormal (tp, np, bp)
+    const G cs = ca * sdn, q = rsqrt_(cdn * cdn + cs * cs);
+    fr.n = tp * (q * sa * cs) + np * (q * cdn) + bp * (q * ca * cs);
     fr.b = cross(fr.n, fr.t);
     if (gf_out) *gf_out = gfv;
-    if (a_out) *a_out = a;
+    if (cos_out) {
+        *cos_out = ca_;
+        *sin_out = sa_;
+    }
     return fr;
 }
 
 // ---------------------------------------------------------------- shadowing
 
-// Raw ply visibility (Sec. 4.1.4): at angle a around ply 0 of the nominal
-// cross-section, the share of the window [phi - dP, phi + dP] of incident
+// Raw ply visibility (Sec. 4.1.4): at the angle with cosine and sine (na_x,
+// na_y) around ply 0 of the nominal cross-section, the share of the window [phi - dP, phi + dP] of incident
 // 2D directions (measured from the local normal) that is neither below the
 // ply's tangent line nor towards another ply's disc.  Each occluded set
 // meets the window in at most one piece (the window is shorter than the
 // gap between a set's 2 pi copies); the union length uses a sorting network.
 template <class G, int MP>
-__host__ __device__ inline G ply_shadow_raw(int Np, G rp, G Rpc, G dP, G a, G phi, const double* ply_c,
+__host__ __device__ inline G ply_shadow_raw(int Np, G rp, G Rpc, G dP, G na_x, G na_y, G phi, const double* ply_c,
                                             const double* ply_s)
 {
     G lo[MP], hi[MP];
     G wlo = phi - dP, whi = phi + dP;
-    G na_x, na_y;
-    sincos_turns_g(a * G(kInvTwoPi), &na_y, &na_x);
     G Px = Rpc + rp * na_x, Py = rp * na_y;
     const G big = G(1e30);
 #pragma unroll
@@ -534,7 +550,10 @@ template <class G, class S, int MP> struct XState {
     V3<S> wi_s;
     S Gp, Gf, mu_i;
     S w[4];           // lobe selection weights
-    G a;
+    // terms of the lobes at x that do not depend on wo: Smith's G1 towards wi
+    // (isotropic), 1 / (4 mu_i), and the reflected body lobe's factor
+    S g1i, q4, body;
+    G ca, sa;         // angle around the hit ply
     G rawp, rawf;     // visibilities before the density blends
 };
 
@@ -548,6 +567,11 @@ __host__ __device__ inline void lobe_weights(const Derived<G, S>& P, XState<G, S
     X.w[1] = (S(1) - P.B) * (S(1) - PR);
     X.w[2] = P.B * P.r;
     X.w[3] = P.B * (S(1) - P.r);
+    const bool front = val(X.mu_i) > 0.0f;
+    const G iz = dot(X.wi_g, X.fx.n);
+    X.g1i = front ? smith_G1_front<S>(X.mu_i, Narrow<S>::from(one_minus_sq(iz)), P.ax) : S(0);
+    X.q4 = front ? rcp_(S(4) * X.mu_i) : S(0);
+    X.body = P.B * P.r * rcp_(S(1) + ls_albedo<S>(front ? X.mu_i : S(0)));
 }
 
 template <class G, class S, int MP, class Tab>
@@ -562,7 +586,7 @@ __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const 
     for (int k = 0; k < MP; ++k)
         if (k == X.ph.ks) { cth = X.ph.cth[k]; sth = X.ph.sth[k]; }
     G gft;
-    X.fx = fiber_frame(P, tab, cth, sth, X.ph.ks, X.ph.n2x, X.ph.n2y, X.ph.vhit, &gft, &X.a);
+    X.fx = fiber_frame(P, tab, cth, sth, X.ph.ks, X.ph.n2x, X.ph.n2y, X.ph.vhit, &gft, &X.ca, &X.sa);
     X.fxs = narrowf<S>(X.fx);
     // shadowing in the geometry scalar: a mostly occluded window leaves a
     // small visible share that single precision cannot resolve
@@ -570,7 +594,7 @@ __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const 
     {
         StageMark<G> mark(kStageShadow);
         G phi = atan2_(X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x, X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y);
-        raw = ply_shadow_raw<G, MP>(P.Np, P.rp, P.Rpc, G(val(P.dP)), X.a, phi, P.ply_c, P.ply_s);
+        raw = ply_shadow_raw<G, MP>(P.Np, P.rp, P.Rpc, G(val(P.dP)), X.ca, X.sa, phi, P.ply_c, P.ply_s);
     }
     X.rawp = raw;
     X.rawf = gft;
@@ -617,8 +641,9 @@ inline void fill_node_disk(TypeRec& t)
             node_lattice(k, t.K, 0.0f, 0.0f, false, xi1, xi2);
             vndf_disk<double>(xi1, xi2, d1, d2);
         }
-        t.node_disk[2 * k] = d1;
-        t.node_disk[2 * k + 1] = d2;
+        t.node_disk[3 * k] = d1;
+        t.node_disk[3 * k + 1] = d2;
+        t.node_disk[3 * k + 2] = sqrt(1.0 - d1 * d1);
     }
 }
 
@@ -627,6 +652,10 @@ template <class G, class S> struct Node {
     V3<G> wt;        // refracted direction
     Frame<G> fy;     // fiber frame at the exit point
     V3<G> y;         // exit point (x, y, height)
+    // terms of the exit refraction that do not depend on wo: wt.n_y, wt.wt,
+    // Smith's G1 towards -wt (isotropic)
+    G ti, ii;
+    S g1;
 };
 
 // Node k of the integral over exit points (Eq. 1): a visible normal at x
@@ -653,19 +682,23 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
     r.fy.n = -X.fx.n;
     r.fy.b = cross(r.fy.n, r.fy.t);
     r.y = mk3<G>(ph.p2x, ph.p2y, ph.vhit);
+    r.ti = r.ii = G(0);
+    r.g1 = S(0);
     if (val(X.mu_i) > 0.0f) {
         StageMark<G> mark(kStageRefract);
         V3<G> wl = to_local(X.fx, X.wi_g);
-        G d1, d2;
+        G d1, d2, r1;
         if (disk && !has_shift) {
-            d1 = G(disk[2 * k]);
-            d2 = G(disk[2 * k + 1]);
+            d1 = G(disk[3 * k]);
+            d2 = G(disk[3 * k + 1]);
+            r1 = G(disk[3 * k + 2]);
         } else {
             double xi1, xi2;
             node_lattice(k, P.K, s0, s1, has_shift, xi1, xi2);
             vndf_disk<G>(G(xi1), G(xi2), d1, d2);
+            r1 = sqrt_(G(1) - d1 * d1);
         }
-        V3<G> ml = sample_vndf_disk<G>(wl, P.ax_g, P.ay_g, d1, d2);
+        V3<G> ml = sample_vndf_disk<G>(wl, P.ax_g, P.ay_g, d1, d2, r1);
         V3<G> m = to_world(X.fx, ml);
         G c = dot(X.wi_g, m);
         c = val(c) > 0.0 ? c : G(0);
@@ -683,7 +716,7 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
         } else {
             g1t = smith_G1<S>(narrow3<S>(to_local(X.fx, wt)), narrow3<S>(ml), P.ax, P.ay);
         }
-        r.T = fresnel_T<S>(cs, P.eta) * g1t;
+        r.T = fresnel_T<S>(cs, P.eta, P.inv_eta2) * g1t;
         // chord in the projected cross-section, starting at the ply hit
         StageMark<G> chord_mark(kStageChord);
         G le2 = wt.x * wt.x + wt.y * wt.y;
@@ -697,7 +730,7 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
             G dq = bq * bq - cq;
             G syarn = -bq + (val(dq) > 0.0 ? sqrt_(dq) : G(0));
             int N = 0, jl = -1;
-            G sbest = G(0), cxl = G(0), cyl = G(0), cthl = G(0), sthl = G(0);
+            G sbest = G(0), cthl = G(0), sthl = G(0);
 #pragma unroll
             for (int j = 0; j < MP; ++j) {
                 if (j >= P.Np) break;
@@ -727,8 +760,6 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
                     if (jl < 0 || val(so) > val(sbest)) {
                         jl = j;
                         sbest = so;
-                        cxl = P.Rpc * ph.cth[j];
-                        cyl = P.Rpc * ph.sth[j];
                         cthl = ph.cth[j];
                         sthl = ph.sth[j];
                     }
@@ -737,13 +768,17 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
             G y2x = ph.p2x + sbest * ex, y2y = ph.p2y + sbest * ey;
             G ell = sbest * il;
             G zy = ph.vhit + wt.z * ell;
-            G nyx = y2x - cxl, nyy = y2y - cyl;
+            G nyx = y2x - P.Rpc * cthl, nyy = y2y - P.Rpc * sthl;
             G ninv = rsqrt_(nyx * nyx + nyy * nyy);
             r.att = exp_(-P.sigma_t * Narrow<S>::from(ell) * S(float(N)));
             r.fy = fiber_frame<G, S, Tab>(P, tab, cthl, sthl, jl, nyx * ninv, nyy * ninv, zy, nullptr,
-                                          nullptr);
+                                          nullptr, nullptr);
             r.y = mk3<G>(y2x, y2y, zy);
         }
+        StageMark<G> exit_mark(kStageExit);
+        r.ti = dot(r.wt, r.fy.n);
+        r.ii = dot(r.wt, r.wt);
+        r.g1 = smith_G1_front<S>(Narrow<S>::from(r.ti), Narrow<S>::from(one_minus_sq(r.ti)), P.ax);
     }
     nd = r;
 }
@@ -753,45 +788,77 @@ __host__ __device__ inline void forward_node(const Derived<G, S>& P, const Tab& 
 // wo through this node.  The half vector, the cosines and the transmittance
 // use the geometry scalar: next to the critical angle the transmittance
 // falls like the transmitted cosine, whose derivative is unbounded.
+//
+// With an isotropic roughness everything follows from the scalars wt.n, wo.n,
+// wt.wt, wt.wo and wo.wo: h = eta wt - wo has |h|^2 = eta^2 wt.wt -
+// 2 eta wt.wo + wo.wo, the denominator (eta wi'.m + wo.m)^2 of the Jacobian
+// is |h|^2 itself, and no vector is formed (half of the operations; 18 fewer
+// per node and direction).  |h|^2 cancels to (eta - 1)^2 when wo continues
+// wt, so indices below kExitScalarEta, where that would cost more than two
+// digits, take the vectors like the anisotropic case.
+constexpr double kExitScalarEta = 1.25;
 template <class G, class S>
-__host__ __device__ inline void exit_btdf(const Derived<G, S>& P, const V3<G>& wt, const Frame<G>& fy,
-                                          const V3<G>& wo, S* val_out, S* pdf_out)
+__host__ __device__ inline void exit_btdf(const Derived<G, S>& P, const Node<G, S>& nd, const V3<G>& wo, const G& co,
+                                          S* val_out, S* pdf_out)
 {
     StageMark<G> mark(kStageExit);
     *val_out = S(0);
     *pdf_out = S(0);
-    V3<G> wip = -wt;
-    G ci = dot(wip, fy.n), co = dot(wo, fy.n);
-    if (!(val(ci) < 0.0 && val(co) > 0.0)) return;
-    V3<G> mh = -(wip * P.eta_g + wo);
-    G ml2 = dot(mh, mh);
-    if (!(val(ml2) > 0.0)) return;
-    mh = mh * rsqrt_(ml2);
-    G mz = dot(mh, fy.n);
-    if (val(mz) < 0.0) {
-        mh = -mh;
-        mz = -mz;
-    }
-    G im = dot(wip, mh), om = dot(wo, mh);
-    if (!(val(im) < 0.0 && val(om) > 0.0)) return;
-    G den = P.eta_g * im + om;
-    G Ft = fresnel_T<G>(-im, P.inv_eta_g);
-    S D, g1i, g1o;
-    if (val(P.ax) == val(P.ay)) {
+    if (!(val(nd.ti) > 0.0 && val(co) > 0.0)) return;
+    const Frame<G>& fy = nd.fy;
+    const G eta2 = P.eta_g * P.eta_g;
+    S D, g1i, g1o, geo;
+    G im;
+    if (val(P.ax) == val(P.ay) && val(P.eta_g) >= kExitScalarEta) {
+        const G c = dot(nd.wt, wo), ww = dot(wo, wo);
+        const G hi = c - P.eta_g * nd.ii, ho = P.eta_g * c - ww;  // wi'.h, wo.h
+        const G l2 = ww - P.eta_g * (c + hi);
+        if (!(val(l2) > 0.0)) return;
+        const G il = rsqrt_(l2);
+        G mz = (P.eta_g * nd.ti - co) * il;
+        im = hi * il;
+        G om = ho * il;
+        if (val(mz) < 0.0) {
+            mz = -mz;
+            im = -im;
+            om = -om;
+        }
+        if (!(val(im) < 0.0 && val(om) > 0.0)) return;
         D = ggx_D_iso<S>(Narrow<S>::from(mz), Narrow<S>::from(one_minus_sq(mz)), P.ax);
-        g1i = smith_G1_iso<S>(Narrow<S>::from(im), Narrow<S>::from(ci), Narrow<S>::from(one_minus_sq(ci)),
-                              P.ax);
-        g1o = smith_G1_iso<S>(Narrow<S>::from(om), Narrow<S>::from(co), Narrow<S>::from(one_minus_sq(co)),
-                              P.ax);
+        g1i = nd.g1;
+        g1o = smith_G1_front<S>(Narrow<S>::from(co), Narrow<S>::from(one_minus_sq(co)), P.ax);
+        geo = Narrow<S>::from((hi * ho) * -rcp_(nd.ti * (l2 * l2)));
     } else {
-        V3<S> ml = narrow3<S>(to_local(fy, mh));
-        D = ggx_D<S>(ml, P.ax, P.ay);
-        g1i = smith_G1<S>(narrow3<S>(to_local(fy, wip)), ml, P.ax, P.ay);
-        g1o = smith_G1<S>(narrow3<S>(to_local(fy, wo)), ml, P.ax, P.ay);
+        const V3<G> wip = -nd.wt;
+        const G ci = -nd.ti;
+        V3<G> mh = -(wip * P.eta_g + wo);
+        G ml2 = dot(mh, mh);
+        if (!(val(ml2) > 0.0)) return;
+        mh = mh * rsqrt_(ml2);
+        G mz = dot(mh, fy.n);
+        if (val(mz) < 0.0) {
+            mh = -mh;
+            mz = -mz;
+        }
+        im = dot(wip, mh);
+        const G om = dot(wo, mh);
+        if (!(val(im) < 0.0 && val(om) > 0.0)) return;
+        const G den = P.eta_g * im + om;
+        if (val(P.ax) == val(P.ay)) {
+            D = ggx_D_iso<S>(Narrow<S>::from(mz), Narrow<S>::from(one_minus_sq(mz)), P.ax);
+            g1i = nd.g1;
+            g1o = smith_G1_front<S>(Narrow<S>::from(co), Narrow<S>::from(one_minus_sq(co)), P.ax);
+        } else {
+            V3<S> ml = narrow3<S>(to_local(fy, mh));
+            D = ggx_D<S>(ml, P.ax, P.ay);
+            g1i = smith_G1<S>(narrow3<S>(to_local(fy, wip)), ml, P.ax, P.ay);
+            g1o = smith_G1<S>(narrow3<S>(to_local(fy, wo)), ml, P.ax, P.ay);
+        }
+        // |wi'.m| |wo.m| / (|wi'.n| |wo.n|) * Jacobian / (eta wi'.m + wo.m)^2,
+        // times |wo.n| for the returned value
+        geo = Narrow<S>::from((im * om) * rcp_(ci * (den * den)));
     }
-    // |wi'.m| |wo.m| / (|wi'.n| |wo.n|) * Jacobian / (eta wi'.m + wo.m)^2,
-    // times |wo.n| for the returned value
-    S geo = Narrow<S>::from((im * om) * rcp_(ci * (den * den)));
+    const G Ft = fresnel_T<G>(-im, P.inv_eta_g, eta2);
     *val_out = geo * Narrow<S>::from(Ft) * g1i * g1o * D;
     *pdf_out = geo * g1i * D;
 }
@@ -830,10 +897,9 @@ __host__ __device__ inline void lobes_at_x(const Derived<G, S>& P, const XState<
         const G ih_g = dot(X.wi_g, hv), oh_g = dot(wo_g, hv);
         S D, g1i, g1o;
         if (val(P.ax) == val(P.ay)) {
-            const G hz = dot(hv, X.fx.n), iz = dot(X.wi_g, X.fx.n);
+            const G hz = dot(hv, X.fx.n);
             D = ggx_D_iso<S>(Narrow<S>::from(hz), Narrow<S>::from(one_minus_sq(hz)), P.ax);
-            g1i = smith_G1_iso<S>(Narrow<S>::from(ih_g), Narrow<S>::from(iz), Narrow<S>::from(one_minus_sq(iz)),
-                                  P.ax);
+            g1i = val(ih_g) > 0.0 ? X.g1i : S(0);
             g1o = smith_G1_iso<S>(Narrow<S>::from(oh_g), mu_o, Narrow<S>::from(one_minus_sq(mu_o_g)), P.ax);
         } else {
             V3<S> hl = narrow3<S>(to_local(X.fx, hv));
@@ -843,15 +909,14 @@ __host__ __device__ inline void lobes_at_x(const Derived<G, S>& P, const XState<
         }
         S ih = Narrow<S>::from(ih_g), oh = Narrow<S>::from(oh_g);
         S ihp = val(ih) > 0.0f ? ih : S(0);
-        const S q4 = rcp_(S(4) * mu_i);
-        ExS = (S(1) - P.B) * P.kS * fresnel<S>(ihp, P.eta) * g1i * g1o * D * q4;
-        if (val(oh) > 0.0f) pxS = g1i * ihp * D * q4 * rcp_(oh);
+        ExS = (S(1) - P.B) * P.kS * fresnel<S>(ihp, P.eta) * g1i * g1o * D * X.q4;
+        if (val(oh) > 0.0f) pxS = g1i * ihp * D * X.q4 * rcp_(oh);
     }
     S bxu = S(0), pxB = S(0);
     if (val(mu_o_g) > 0.0) {
         S mp = front_i ? mu_i : S(0);
         S fls = rcp_(S(float(4.0 * kPi)) * (mp + mu_o));
-        bxu = P.B * P.r * (fls + S(float(1.0 / kPi))) * mu_o * rcp_(S(1) + ls_albedo<S>(mp));
+        bxu = X.body * (fls + S(float(1.0 / kPi))) * mu_o;
         pxB = mu_o * S(float(1.0 / kPi));
     }
     a.ExS = ExS;
@@ -875,7 +940,7 @@ __host__ __device__ inline void lobes_node_step(const Derived<G, S>& P, bool fro
     }
     if (front_i) {
         S vv, pd;
-        exit_btdf(P, nd.wt, nd.fy, wo_g, &vv, &pd);
+        exit_btdf(P, nd, wo_g, cyg, &vv, &pd);
         a.EyS = a.EyS + nd.T * nd.att * vv;
         a.pyS = a.pyS + pd;
         if (dsig && val(nd.att) > 0.0f) *dsig = *dsig + nd.T * nd.att * vv * log_(nd.att);

@@ -101,8 +101,7 @@ __host__ __device__ inline bool stratum_frame(const Derived<G, S>& P, const Tab&
             cth = ph.cth[k];
             sth = ph.sth[k];
         }
-    G a;
-    fx = fiber_frame(P, tab, cth, sth, ph.ks, ph.n2x, ph.n2y, ph.vhit, &rawf, &a);
+    fx = fiber_frame<G, S, Tab>(P, tab, cth, sth, ph.ks, ph.n2x, ph.n2y, ph.vhit, &rawf, nullptr, nullptr);
     return true;
 }
 
