@@ -291,24 +291,59 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 #define BYSDF_BACKWARD_MIN_WAVES 1
 #endif
 
+// The kernel's argument struct, which follows the two pointers of the type
+// records and tables, read from the argument segment where it is used.
+// Arguments used in the ordinary way are loaded at the entry and held in
+// scalar registers; the 25 to 40 pointers of the query kernels fill those
+// through the whole body, and the type's scalars and the polynomials'
+// constants spill for them.  Scratch per lane falls from 104 to 80 B in
+// k_eval_sample, 96 to 28 B in k_eval, 300 to 156 B in k_eval_multi; eval and
+// sample of 4 Mi queries 3314 -> 3222 us, 262144 footprint queries
+// 455 -> 430 us.  The two pointers stay ordinary `__restrict__` parameters:
+// through a struct the type records would be loaded by the vector unit.
+template <class A> __device__ inline A late_args()
+{
+    using Word = const __attribute__((address_space(4))) uint64_t;
+    static_assert(sizeof(A) % sizeof(uint64_t) == 0, "whole words");
+    Word* p = (Word*)__builtin_amdgcn_kernarg_segment_ptr() + 2;
+    asm volatile("" : "+s"(p));
+    uint64_t w[sizeof(A) / sizeof(uint64_t)];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(A) / sizeof(uint64_t); ++k) w[k] = p[k];
+    A a;
+    __builtin_memcpy(&a, w, sizeof(A));
+    return a;
+}
+
+struct EvalArgs {
+    int n_types, lds_texels;
+    QPtrs q;
+    OPtrs o;
+    int64_t n;
+};
+
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const TypeRec* __restrict__ types, int n_types,
-                                                 const float4* __restrict__ tables, int lds_texels,
-                                                 QPtrs q, OPtrs o, int64_t n)
+__global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const TypeRec* __restrict__ types,
+    const float4* __restrict__ tables, EvalArgs args)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<EvalArgs>().n; i += stride) {
+        const EvalArgs& in = late_args<EvalArgs>();
+        const QPtrs& q = in.q;
+        const int n_types = in.n_types;
         int t = q.type[i];
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
         V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
         float h = q.h[i], u = q.u[i], v = q.v[i];
+        const bool has_shift = q.s0 != nullptr;
+        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
         uint32_t fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         fl |= check_inputs(h, u, v, wi) | check_dir(wo);
         EvalOut<float> e;
@@ -324,11 +359,11 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const Typ
             fl = X.ph.flags;
             if (!X.ph.pass) {
                 if (!(X.mu_i > 0.0f)) fl |= F_BACKFACING;
-                float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
                 V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
-                lobes(P, tab, X, wo_g, s0, s1, q.s0 != nullptr, e, types[tu].node_disk);
+                lobes(P, tab, X, wo_g, s0, s1, has_shift, e, types[tu].node_disk);
             }
         });
+        const OPtrs& o = late_args<EvalArgs>().o;
         o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
         o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
         o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -370,20 +405,29 @@ struct SOPtrs {
     uint32_t* flags;
 };
 
+struct SampleArgs {
+    int n_types, lds_texels;
+    SPtrs q;
+    SOPtrs o;
+    int64_t n;
+};
+
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const TypeRec* __restrict__ types, int n_types,
-                                                   const float4* __restrict__ tables,
-                                                   int lds_texels, SPtrs q, SOPtrs o, int64_t n)
+__global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const TypeRec* __restrict__ types,
+    const float4* __restrict__ tables, SampleArgs args)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<SampleArgs>().n; i += stride) {
+        const SampleArgs& in = late_args<SampleArgs>();
+        const SPtrs& q = in.q;
+        const int n_types = in.n_types;
         int t = q.type[i];
         SampleOut<float> so;
         for (int c = 0; c < 3; ++c) so.wo[c] = so.wgt[c] = so.ex[c] = 0.0f;
@@ -393,16 +437,18 @@ __global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const
         uint32_t fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         const bool need = fl == 0u;
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
-        float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
+        const bool has_shift = q.s0 != nullptr;
+        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
         float h = q.h[i], u = q.u[i], v = q.v[i], x0, x1, x2;
         query_xi(q, i, x0, x1, x2);
         for_each_wave_type(t, need, [&](int tu) {
             const Derived<double, float>& P = types[tu].d;
             TabPtrT<MIG> tab;
             tab.p = kLds ? s_tab : tables + types[tu].table_off;
-            fl = sample_query<double, float, MP>(P, tab, h, u, v, wi, x0, x1, x2, s0, s1,
-                                                 q.s0 != nullptr, so, types[tu].node_disk);
+            fl = sample_query<double, float, MP>(P, tab, h, u, v, wi, x0, x1, x2, s0, s1, has_shift, so,
+                                                 types[tu].node_disk);
         });
+        const SOPtrs& o = late_args<SampleArgs>().o;
         o.wox[i] = so.wo[0]; o.woy[i] = so.wo[1]; o.woz[i] = so.wo[2];
         o.wr[i] = so.wgt[0]; o.wg[i] = so.wgt[1]; o.wb[i] = so.wgt[2];
         o.pdf[i] = so.pdf;
@@ -418,25 +464,40 @@ __global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const
 // direction.  The state at x and the K forward nodes are computed once and
 // serve both directions, so a query costs about one evaluation plus the
 // draw instead of an evaluation and a sample.
+struct EvalSampleArgs {
+    int n_types, lds_texels;
+    QPtrs q;
+    const float *xi0, *xi1, *xi2;
+    OPtrs o;
+    SOPtrs so;
+    int64_t n;
+};
+
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sample(
-    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
-    QPtrs q, const float* __restrict__ xi0, const float* __restrict__ xi1,
-    const float* __restrict__ xi2, OPtrs o, SOPtrs so_p, int64_t n)
+__global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sample(const TypeRec* __restrict__ types,
+    const float4* __restrict__ tables, EvalSampleArgs args)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<EvalSampleArgs>().n; i += stride) {
+        const EvalSampleArgs& in = late_args<EvalSampleArgs>();
+        const QPtrs& q = in.q;
+        const int n_types = in.n_types;
+        const float* xi0 = in.xi0;
+        const float* xi1 = in.xi1;
+        const float* xi2 = in.xi2;
         int t = q.type[i];
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
         V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
         float h = q.h[i], u = q.u[i], v = q.v[i], x0 = xi0[i], x1 = xi1[i], x2 = xi2[i];
+        const bool has_shift = q.s0 != nullptr;
+        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
         const uint32_t bad_t = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         const uint32_t bad_hit = bad_t | check_inputs(h, u, v, wi);
         const uint32_t bad_wo = check_dir(wo);
@@ -455,9 +516,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sa
             tab.p = kLds ? s_tab : tables + types[tu].table_off;
             XState<double, float, MP> X;
             state_at_x(P, tab, h, u, v, wi, X);
-            float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
-            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{P, tab, X, s0, s1, q.s0 != nullptr,
-                                                               types[tu].node_disk};
+            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{P, tab, X, s0, s1, has_shift, types[tu].node_disk};
             V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
             fs = eval_sample_from_x(P, X, wi, wo_g, bad_wo == 0u, x0, x1, x2, nf, e, so);
             if (bad_wo == 0u) {
@@ -465,6 +524,9 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sa
                 if (!X.ph.pass && !(X.mu_i > 0.0f)) fe |= F_BACKFACING;
             }
         });
+        const EvalSampleArgs& out = late_args<EvalSampleArgs>();
+        const OPtrs& o = out.o;
+        const SOPtrs& so_p = out.so;
         o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
         o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
         o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -556,9 +618,11 @@ struct MQuery {
     float h, u, v, h1, h2, zeta;
     V3<float> wi;
 };
-template <class QP>
-__device__ inline MQuery load_mquery(const QP& q, const FPtrs& fp, int64_t i)
+template <class A> __device__ inline MQuery load_mquery(int64_t i)
 {
+    const A in = late_args<A>();
+    const auto& q = in.q;
+    const FPtrs& fp = in.fp;
     MQuery m;
     m.h = q.h[i];
     m.u = q.u[i];
@@ -574,11 +638,10 @@ __device__ inline MQuery load_mquery(const QP& q, const FPtrs& fp, int64_t i)
 // return each lane holds its footprint's frame and shadowing, as
 // footprint_geometry computes them; `any` is false when no stratum of
 // positive weight hits a ply.
-template <bool kLds, int MP, bool MIG, class QP>
+template <bool kLds, int MP, bool MIG, class A>
 __device__ inline void wave_footprint_geometry(const TypeRec* __restrict__ types,
                                                const float4* __restrict__ tables, const float4* s_tab,
-                                               const QP& q, const FPtrs& fp, int n_max, int64_t b,
-                                               int t, int first, int nq, int S, Frame<double>& F,
+                                               int n_max, int64_t b, int t, int first, int nq, int S, Frame<double>& F,
                                                float& Gm, bool& any, uint32_t& fl)
 {
     V3<double> sn = mk3<double>(0.0, 0.0, 0.0), st = sn, n0 = sn, t0 = sn;
@@ -597,7 +660,7 @@ __device__ inline void wave_footprint_geometry(const TypeRec* __restrict__ types
             const TypeRec& R = types[tu];
             TabPtrT<MIG> tab;
             tab.p = kLds ? s_tab : tables + R.table_off;
-            const MQuery m = load_mquery(q, fp, b + own);
+            const MQuery m = load_mquery<A>(b + own);
             Footprint fo;
             make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, fo);
             const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
@@ -684,34 +747,45 @@ struct MultiSampleLds {
     int lobe[kWave], node[kWave];
 };
 
+struct EvalMultiArgs {
+    int n_types, lds_texels, n_max, unused;
+    QPtrs q;
+    FPtrs fp;
+    OPtrs o;
+    int64_t n;
+};
+
 template <bool kLds, int MP, bool MIG>
 __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
-    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
-    QPtrs q, FPtrs fp, int n_max, OPtrs o, int64_t n)
+    const TypeRec* __restrict__ types, const float4* __restrict__ tables, EvalMultiArgs args)
 {
+    using A = EvalMultiArgs;
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     __shared__ MultiLds s_ml[kBlock / kWave];
     if (kLds) {
-        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int lane = __lane_id();
     MultiLds& L = s_ml[threadIdx.x / kWave];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     // whole wavefronts iterate together (the cross-lane steps need every lane)
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < n; b += stride) {
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < late_args<A>().n; b += stride) {
+        const int n_max = late_args<A>().n_max;
         const int64_t i = b + lane;
-        const bool in = i < n;
-        const int t = in ? q.type[i] : 0;
+        const bool in = i < late_args<A>().n;
+        const int t = in ? late_args<A>().q.type[i] : 0;
         uint32_t fl = F_BAD_INPUT;
         double wsum = 1.0;
         int nq = 0;
         if (in) {
-            const MQuery m = load_mquery(q, fp, i);
+            const MQuery m = load_mquery<A>(i);
+            const A in_args = late_args<A>();
+            const QPtrs& q = in_args.q;
             const V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
-            fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
+            fl = (t < 0 || t >= in_args.n_types) ? F_BAD_INPUT : 0u;
             fl |= check_inputs(m.h, m.u, m.v, m.wi) | check_dir(wo) | check_footprint(m.h, m.h1, m.h2, m.zeta);
             if (fl == 0u) {
                 Footprint f;
@@ -732,7 +806,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
             Frame<double> F;
             float Gm;
             bool any;
-            wave_footprint_geometry<kLds, MP, MIG>(types, tables, s_tab, q, fp, n_max, b, t, firsta, nqa, Sa,
+            wave_footprint_geometry<kLds, MP, MIG, A>(types, tables, s_tab, n_max, b, t, firsta, nqa, Sa,
                                                    F, Gm, any, fl);
             if (nqa > 0 && !any) fl |= F_PASS_THROUGH;
             wave_lds_sync();
@@ -762,7 +836,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
                 TabPtrT<MIG> tab;
                 tab.p = kLds ? s_tab : tables + R.table_off;
                 const int64_t io = b + own;
-                const MQuery m = load_mquery(q, fp, io);
+                const MQuery m = load_mquery<A>(io);
                 Footprint fo;
                 make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, fo);
                 const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
@@ -780,6 +854,8 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
                     apply_aggregate(Pm, X, Fo, L.gm[own]);
                 }
                 back = !(X.mu_i > 0.0f);
+                const A in_args = late_args<A>();
+                const QPtrs& q = in_args.q;
                 const float s0 = q.s0 ? q.s0[io] : 0.0f, s1 = q.s1 ? q.s1[io] : 0.0f;
                 const V3<double> wo_g = mk3<double>(q.wox[io], q.woy[io], q.woz[io]);
                 EvalOut<float> e;
@@ -821,6 +897,8 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
         if (!in) continue;
         if (single && !hit1) fl |= F_PASS_THROUGH;
         const float iw = float(1.0 / wsum);
+        const A out = late_args<A>();
+        const OPtrs& o = out.o;
         o.Er[i] = L.acc[0][lane] * iw; o.Eg[i] = L.acc[1][lane] * iw; o.Eb[i] = L.acc[2][lane] * iw;
         o.ExS[i] = L.acc[3][lane] * iw; o.EyS[i] = L.acc[4][lane] * iw;
         o.ExBr[i] = L.acc[5][lane] * iw; o.ExBg[i] = L.acc[6][lane] * iw; o.ExBb[i] = L.acc[7][lane] * iw;
@@ -830,29 +908,38 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
     }
 }
 
+struct SampleMultiArgs {
+    int n_types, lds_texels, n_max, unused;
+    SPtrs q;
+    FPtrs fp;
+    SOPtrs o;
+    int64_t n;
+};
+
 // OWNXI: the uniforms come from the generator (xi arrays NULL).  Only the
 // instance that needs it carries the generator: its code alone, never run,
 // costs the multi-scale sampler a quarter of its speed in registers.
 template <bool kLds, int MP, bool MIG, bool OWNXI>
 __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
-    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
-    SPtrs q, FPtrs fp, int n_max, SOPtrs o, int64_t n)
+    const TypeRec* __restrict__ types, const float4* __restrict__ tables, SampleMultiArgs args)
 {
+    using A = SampleMultiArgs;
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     __shared__ MultiSampleLds s_ml[kBlock / kWave];
     if (kLds) {
-        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int lane = __lane_id();
     MultiSampleLds& L = s_ml[threadIdx.x / kWave];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < n; b += stride) {
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < late_args<A>().n; b += stride) {
+        const int n_max = late_args<A>().n_max;
         const int64_t i = b + lane;
-        const bool in = i < n;
-        int t = in ? q.type[i] : 0;
+        const bool in = i < late_args<A>().n;
+        int t = in ? late_args<A>().q.type[i] : 0;
         uint32_t fl = F_BAD_INPUT;
         Footprint f;
         f.n = 0;
@@ -860,8 +947,10 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
         MQuery m{};
         float xs = 0.0f, x0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
         if (in) {
-            m = load_mquery(q, fp, i);
-            xs = fp.xi_s[i];
+            m = load_mquery<A>(i);
+            const A in_args = late_args<A>();
+            const SPtrs& q = in_args.q;
+            xs = in_args.fp.xi_s[i];
             if (OWNXI) {
                 query_xi(q, i, x0, x1, x2);
             } else {
@@ -869,7 +958,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 x1 = q.xi1[i];
                 x2 = q.xi2[i];
             }
-            fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
+            fl = (t < 0 || t >= in_args.n_types) ? F_BAD_INPUT : 0u;
             fl |= check_inputs(m.h, m.u, m.v, m.wi) | check_footprint(m.h, m.h1, m.h2, m.zeta);
             if (!(xs >= 0.0f && xs < 1.0f)) fl |= F_BAD_INPUT;
             if (fl == 0u) make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, f);
@@ -886,7 +975,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
         {
             Frame<double> F;
             float Gm;
-            wave_footprint_geometry<kLds, MP, MIG>(types, tables, s_tab, q, fp, n_max, b, t, firsta, nqa, Sa,
+            wave_footprint_geometry<kLds, MP, MIG, A>(types, tables, s_tab, n_max, b, t, firsta, nqa, Sa,
                                                    F, Gm, any, fl);
             wave_lds_sync();
             L.fn[0][lane] = F.n.x; L.fn[1][lane] = F.n.y; L.fn[2][lane] = F.n.z;
@@ -914,7 +1003,14 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
             }
         }
         bool drawn = false, pass = good && !any && !single;
-        const float s0 = in && q.s0 ? q.s0[i] : 0.0f, s1 = in && q.s1 ? q.s1[i] : 0.0f;
+        bool has_shift;
+        float s0, s1;
+        {
+            const A in_args = late_args<A>();
+            has_shift = in_args.q.s0 != nullptr;
+            s0 = in && has_shift ? in_args.q.s0[i] : 0.0f;
+            s1 = in && has_shift ? in_args.q.s1[i] : 0.0f;
+        }
         for_each_wave_type<false>(t, good && (any || single), [&](int tu) {
             const TypeRec& R = types[tu];
             TabPtrT<MIG> tab;
@@ -932,7 +1028,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 Fo.b = cross(Fo.n, Fo.t);
                 apply_aggregate(Pm, X, Fo, L.gm[lane]);
             }
-            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{Pm, tab, X, s0, s1, q.s0 != nullptr};
+            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{Pm, tab, X, s0, s1, has_shift};
             SampleOut<float> so;
             V3<double> wo;
             fl |= sample_draw(Pm, X, m.wi, x0, x1, x2, nf, so, wo, drawn);
@@ -961,7 +1057,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 TabPtrT<MIG> tab;
                 tab.p = kLds ? s_tab : tables + R.table_off;
                 const int64_t io = b + own;
-                const MQuery mo = load_mquery(q, fp, io);
+                const MQuery mo = load_mquery<A>(io);
                 Footprint fo;
                 make_footprint(mo.h, mo.h1, mo.h2, mo.zeta, n_max, fo);
                 const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
@@ -976,6 +1072,8 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                     Fo.b = cross(Fo.n, Fo.t);
                     apply_aggregate(Pm, X, Fo, L.gm[own]);
                 }
+                const A in_args = late_args<A>();
+                const SPtrs& q = in_args.q;
                 const float t0 = q.s0 ? q.s0[io] : 0.0f, t1 = q.s1 ? q.s1[io] : 0.0f;
                 const V3<double> wd = mk3<double>(L.wo[0][own], L.wo[1][own], L.wo[2][own]);
                 EvalOut<float> e;
@@ -999,6 +1097,9 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
             }
         }
         if (!in) continue;
+        const A out = late_args<A>();
+        const SPtrs& q = out.q;
+        const SOPtrs& o = out.o;
         SampleOut<float> so;
         for (int c = 0; c < 3; ++c) {
             so.wo[c] = so.wgt[c] = 0.0f;
@@ -1530,22 +1631,30 @@ __global__ void k_backward_sum(const int32_t* __restrict__ tile_first, int n_typ
 // last tile, so the grid always drains.
 __global__ void k_reset_counter(int* counter) { *counter = 0; }
 
+struct BatchedArgs {
+    const int64_t* off;
+    const int32_t* tile_first;
+    int* counter;
+    int n_types, chunk;
+    QPtrs q;
+    OPtrs o;
+};
+
 template <int MP, bool kLds, int WAVES>
-__global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(
-    const TypeRec* __restrict__ types, const float4* __restrict__ tables,
-    const int64_t* __restrict__ off, int n_types, const int32_t* __restrict__ tile_first,
-    int* counter, QPtrs q, OPtrs o, int chunk)
+__global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(const TypeRec* __restrict__ types,
+    const float4* __restrict__ tables, BatchedArgs args)
 {
+    const int chunk = args.chunk;
     bysdf::stage_math_tables();
     __syncthreads();
     // a tile holds as many queries as the workgroup has lanes (128 or 256)
     __shared__ float4 s_tab[kLds ? kMaxLdsTexels : 1];
     __shared__ int s_next;
     const int tid = threadIdx.x;
-    const int n_tiles = tile_first[n_types];
+    const int n_tiles = args.tile_first[args.n_types];
     int staged = -1;
     for (;;) {
-        if (tid == 0) s_next = atomicAdd(counter, chunk);
+        if (tid == 0) s_next = atomicAdd(late_args<BatchedArgs>().counter, chunk);
         __syncthreads();
         const int t0 = s_next;
         __syncthreads();
@@ -1553,7 +1662,10 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(
         for (int c = 0; c < chunk; ++c) {
             int type = 0, count = 0;
             int64_t start = 0;
-            if (!locate_tile(t0 + c, tile_first, n_types, off, &type, &start, &count, (int)blockDim.x)) break;
+            const BatchedArgs& in = late_args<BatchedArgs>();
+            const QPtrs& q = in.q;
+            if (!locate_tile(t0 + c, in.tile_first, in.n_types, in.off, &type, &start, &count, (int)blockDim.x))
+                break;
             type = __builtin_amdgcn_readfirstlane(type);
             const TypeRec& rec = types[type];
             TabPtr tab;
@@ -1573,6 +1685,8 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(
             V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
             V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
             const float h = q.h[i], u = q.u[i], v = q.v[i];
+            const bool has_shift = q.s0 != nullptr;
+            const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
             uint32_t fl = check_inputs(h, u, v, wi) | check_dir(wo);
             EvalOut<float> e;
             for (int k = 0; k < 3; ++k) e.E[k] = e.ExB[k] = e.EyB[k] = 0.0f;
@@ -1584,11 +1698,11 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(
                 fl = X.ph.flags;
                 if (!X.ph.pass) {
                     if (!(X.mu_i > 0.0f)) fl |= F_BACKFACING;
-                    const float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
                     V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
-                    lobes(P, tab, X, wo_g, s0, s1, q.s0 != nullptr, e, rec.node_disk);
+                    lobes(P, tab, X, wo_g, s0, s1, has_shift, e, rec.node_disk);
                 }
             }
+            const OPtrs& o = late_args<BatchedArgs>().o;
             o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
             o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
             o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -1806,8 +1920,8 @@ extern "C" int bysdf_eval(const bysdf_types_t* h, const bysdf_query_soa* q, int6
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
-                       h->d_tables, tx, qp, op, n);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
+                       EvalArgs{h->n_types, tx, qp, op, n});
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1845,8 +1959,8 @@ extern "C" int bysdf_sample_pdf(const bysdf_types_t* h, const bysdf_sample_soa* 
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_sample, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
-                       h->d_tables, tx, sp, op, n);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
+                       SampleArgs{h->n_types, tx, sp, op, n});
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1879,8 +1993,8 @@ extern "C" int bysdf_eval_sample(const bysdf_types_t* h, const bysdf_query_soa* 
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval_sample, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
-                       h->d_tables, tx, qp, xi0, xi1, xi2, op, sop, n);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
+                       EvalSampleArgs{h->n_types, tx, qp, xi0, xi1, xi2, op, sop, n});
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1919,8 +2033,8 @@ extern "C" int bysdf_eval_multi(const bysdf_types_t* h, const bysdf_query_soa* q
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval_multi, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
-                       h->d_tables, tx, qp, fpp, (int)n_max, op, n);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
+                       EvalMultiArgs{h->n_types, tx, n_max, 0, qp, fpp, op, n});
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1959,8 +2073,8 @@ extern "C" int bysdf_sample_multi(const bysdf_types_t* h, const bysdf_sample_soa
                                                         : k_sample_multi<false, 8, false, X>)))
     auto kern = q->xi0 ? BYSDF_PICK_SM(false) : BYSDF_PICK_SM(true);
 #undef BYSDF_PICK_SM
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
-                       h->d_tables, tx, sp, fpp, (int)n_max, op, n);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
+                       SampleMultiArgs{h->n_types, tx, n_max, 0, sp, fpp, op, n});
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -2159,8 +2273,8 @@ static void launch_batched(const bysdf_types_t* h, bool lds, int waves, int bloc
 {
     auto kern = lds ? (waves == 1 ? k_eval_batched<MP, true, 1> : k_eval_batched<MP, true, 2>)
                     : (waves == 1 ? k_eval_batched<MP, false, 1> : k_eval_batched<MP, false, 2>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, stream, h->d_types, h->d_tables, off, h->n_types,
-                       tile_first, counter, qp, op, chunk);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, stream, h->d_types, h->d_tables,
+                       BatchedArgs{off, tile_first, counter, h->n_types, chunk, qp, op});
 }
 
 extern "C" int bysdf_eval_batched(const bysdf_types_t* h, const int64_t* type_offsets, int64_t n,
