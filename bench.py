@@ -43,7 +43,7 @@ PEAK_HBM_GBS = 8000.0
 
 # sources the BYSDF kernels are built from: counters taken on another
 # version of these no longer describe the kernels
-_KERNEL_SOURCES = ("bysdf_lib.hip", "bysdf_math.hpp", "bysdf_model.hpp", "bysdf_dual.hpp",
+_KERNEL_SOURCES = ("bysdf_lib.hip", "bysdf_math.hpp", "bysdf_model.hpp", "bysdf_adjoint.hpp",
                    "bysdf_opcount.hpp")
 
 

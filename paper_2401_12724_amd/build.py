@@ -20,7 +20,7 @@ LIB = os.path.join(HERE, "libbysdf.so")
 SOURCES = ["bysdf_lib.hip", "yarn_scene.hip", "render.hip"]
 AUDIT_SOURCE = "precision_audit.hip"
 AUDIT_LIB = os.path.join(HERE, "libbysdf_audit.so")
-HEADERS = ["bysdf_math.hpp", "math_tables.inc", "bysdf_model.hpp", "bysdf_multi.hpp", "bysdf_opcount.hpp", "bysdf_dual.hpp",
+HEADERS = ["bysdf_math.hpp", "math_tables.inc", "bysdf_model.hpp", "bysdf_multi.hpp", "bysdf_opcount.hpp", "bysdf_adjoint.hpp",
            "yarn_tube.hpp", "yarn_build.hpp", "philox.hpp",
            "lib_internal.hpp", "bysdf_precision.hpp"]
 

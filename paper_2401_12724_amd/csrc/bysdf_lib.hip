@@ -27,7 +27,7 @@
 #include "bysdf_model.hpp"
 #include "bysdf_multi.hpp"
 #include "bysdf_opcount.hpp"
-#include "bysdf_dual.hpp"
+#include "bysdf_adjoint.hpp"
 #include "lib_internal.hpp"
 
 using namespace bysdf;
@@ -86,6 +86,7 @@ struct bysdf_types {
     int32_t max_plies = 0, max_K = 0;
     int32_t single_table = 0;   // every type uses table 0
     int32_t any_mig = 0;        // some type has fiber migration
+    int32_t any_aniso = 0;      // some type's roughness differs across the fiber
     int32_t table_texels = 0;   // texels of table 0 (LDS staging size)
     int device = 0;
     TypeRec* d_types = nullptr;
@@ -274,7 +275,7 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 // 200-350 B per lane.  With the single-type path of the type waterfall, two
 // wavefronts win for the eval (4.09 ms), the sampler (5.47 -> 4.88 ms), the
 // fused eval + sample (4.43 ms) and the batched eval (20.2 -> 14.7 ms on
-// 2^26 queries); one wins for the adjoint passes.
+// 2^26 queries); one wins for the adjoint (4 Mi queries: 2.6 ms, 4.7 at two).
 #ifndef BYSDF_EVAL_MIN_WAVES
 #define BYSDF_EVAL_MIN_WAVES 2
 #endif
@@ -1514,19 +1515,13 @@ __device__ inline bool locate_tile(int tile, const int32_t* __restrict__ tile_fi
 }
 
 // ------------------------------------------------------------------ adjoint
-// One workgroup per tile.  Each lane recomputes its query three times with
-// the tangent seeded on beta, ply twist and fiber twist (forward-mode dual
-// scalars through the same model, shadowing included), contracts the
-// tangents of E with grad_E, and adds the closed-form derivatives of the
-// linear parameters (albedo, densities).  The tile's lanes reduce in a
+// One workgroup per tile, one lane per query: the reverse sweep of
+// bysdf_adjoint.hpp for the roughness and the twists, and the closed forms of
+// the linear parameters (albedo, densities).  The tile's lanes reduce in a
 // fixed tree order to one partial per tile.
-// One pass of the adjoint per launch, so that each pass gets the register
-// allocation of its own code: pass 0 differentiates beta (and writes the
-// closed forms of the albedo and the densities), pass 1 the ply twist,
-// pass 2 the fiber twist.  Parts of the model that do not depend on the
-// seeded parameter run in plain arithmetic and are promoted to duals with
-// zero tangents: everything at x for beta, the ply hit for the fiber twist.
-template <int MP, int PASS>
+// ANISO, MIG: some type is anisotropic, has fiber migration (neither changes
+// after creation); their code alone, never run, costs registers.
+template <int MP, bool ANISO, bool MIG>
 __global__ __launch_bounds__(kBlock, BYSDF_BACKWARD_MIN_WAVES) void k_backward(const TypeRec* __restrict__ types,
                                                      const float4* __restrict__ tables, QPtrs q,
                                                      const int64_t* __restrict__ off, int n_types,
@@ -1537,20 +1532,17 @@ __global__ __launch_bounds__(kBlock, BYSDF_BACKWARD_MIN_WAVES) void k_backward(c
 {
     bysdf::stage_math_tables();
     __syncthreads();
-    constexpr int NS = PASS == 0 ? 6 : 1;
-    // theta slots written by this pass
-    constexpr int kSlot0[6] = {0, 1, 2, 3, 6, 7};
-    __shared__ float s_red[NS][kBlock];
+    __shared__ float s_red[8][kBlock];
     int t = 0, count = 0;
     int64_t start = 0;
     if (!locate_tile(blockIdx.x, tile_first, n_types, off, &t, &start, &count)) return;
     t = __builtin_amdgcn_readfirstlane(t);
     const int tid = threadIdx.x;
     const TypeRec& rec = types[t];
-    TabPtr tab;
+    TabPtrT<MIG> tab;
     tab.p = tables + rec.table_off;
-    float g[NS];
-    for (int k = 0; k < NS; ++k) g[k] = 0.0f;
+    float g[8];
+    for (int k = 0; k < 8; ++k) g[k] = 0.0f;
     if (tid < count) {
         const int64_t i = start + tid;
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
@@ -1560,53 +1552,36 @@ __global__ __launch_bounds__(kBlock, BYSDF_BACKWARD_MIN_WAVES) void k_backward(c
         if (!bad) {
             const float ge[3] = {gE[3 * i], gE[3 * i + 1], gE[3 * i + 2]};
             const float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
-            V3<DD> wo_d = mk3<DD>(DD((double)wo.x), DD((double)wo.y), DD((double)wo.z));
-            Derived<DD, DF> P = derive_dual(rec, PASS);
-            XState<DD, DF, MP> X;
-            if (PASS == 0) {
-                XState<double, float, MP> Xp;
-                state_at_x(rec.d, tab, h, u, v, wi, Xp);
-                promote(Xp, X);
-                lobe_weights(P, X);  // the terms at x that depend on beta
-            } else if (PASS == 2) {
-                PlyHit<double, MP> ph;
-                trace_plies(rec.d, h, u, v, wi, ph);
-                promote(ph, X.ph);
-                state_after_plies(P, tab, wi, X);
-            } else {
-                state_at_x(P, tab, h, u, v, wi, X);
+            const V3<double> wo_g = mk3<double>((double)wo.x, (double)wo.y, (double)wo.z);
+            float spec = 0.0f, alb = 0.0f;
+            for (int c = 0; c < 3; ++c) {
+                spec += ge[c];
+                alb += ge[c] * rec.d.alb[c];
             }
-            if (!X.ph.pass) {
-                EvalOut<DF> e;
-                lobes(P, tab, X, wo_d, s0, s1, q.s0 != nullptr, e, rec.node_disk);
-                const float dE = ge[0] * e.E[0].d + ge[1] * e.E[1].d + ge[2] * e.E[2].d;
-                if (PASS == 0) {
-                    const float b0 = e.body0.v, Gp = X.Gp.v, Gf = X.Gf.v;
-                    const float op = 1.0f - (float)X.rawp.v, of = 1.0f - (float)X.rawf.v;
-                    float sa = 0.0f;
-                    for (int c = 0; c < 3; ++c) {
-                        g[c] = ge[c] * b0 * Gp * Gf;
-                        sa += ge[c] * rec.d.alb[c];
-                    }
-                    g[3] = dE;
-                    g[4] = -sa * b0 * Gf * op;
-                    g[5] = -sa * b0 * Gp * of;
-                } else {
-                    g[0] = dE;
-                }
+            bysdf::AdjointOut o;
+            const bool hit = !ANISO || rec.d.ax == rec.d.ay
+                ? bysdf::adjoint_query<true, MP>(rec, tab, h, u, v, wi, wo_g, s0, s1, q.s0 != nullptr, spec, alb, o)
+                : bysdf::adjoint_query<false, MP>(rec, tab, h, u, v, wi, wo_g, s0, s1, q.s0 != nullptr, spec, alb, o);
+            if (hit) {
+                for (int c = 0; c < 3; ++c) g[c] = ge[c] * o.body0 * o.Gp * o.Gf;
+                g[3] = (float)o.beta;
+                g[4] = (float)o.ply;
+                g[5] = (float)o.fiber;
+                g[6] = -alb * o.body0 * o.Gf * (1.0f - o.rawp);
+                g[7] = -alb * o.body0 * o.Gp * (1.0f - o.rawf);
             }
         }
         if (per_query)
-            for (int k = 0; k < NS; ++k) per_query[8 * i + (PASS == 0 ? kSlot0[k] : 3 + PASS)] = g[k];
+            for (int k = 0; k < 8; ++k) per_query[8 * i + k] = g[k];
     }
-    for (int k = 0; k < NS; ++k) s_red[k][tid] = g[k];
+    for (int k = 0; k < 8; ++k) s_red[k][tid] = g[k];
     __syncthreads();
     for (int st = kBlock / 2; st > 0; st >>= 1) {
         if (tid < st)
-            for (int k = 0; k < NS; ++k) s_red[k][tid] += s_red[k][tid + st];
+            for (int k = 0; k < 8; ++k) s_red[k][tid] += s_red[k][tid + st];
         __syncthreads();
     }
-    if (tid < NS) partials[8 * (int64_t)blockIdx.x + (PASS == 0 ? kSlot0[tid] : 3 + PASS)] = s_red[tid][0];
+    if (tid < 8) partials[8 * (int64_t)blockIdx.x + tid] = s_red[tid][0];
 }
 
 // grad[t] = sum of the partials of type t's tiles, in tile order
@@ -1796,6 +1771,7 @@ static int types_create(const bysdf_type_params* p, int32_t n_types, bysdf_types
         h->h_type_table.push_back(ti);
         h->max_plies = std::max(h->max_plies, p[i].n_plies);
         if (p[i].mig_tables > 1) h->any_mig = 1;
+        if (p[i].aniso != 1.0f) h->any_aniso = 1;
         h->max_K = std::max(h->max_K, p[i].K);
     }
     h->n_tables = (int32_t)h->h_table_size.size();
@@ -2244,15 +2220,14 @@ extern "C" int bysdf_eval_backward(const bysdf_types_t* h, const bysdf_query_soa
     HIP_TRY(hipGetLastError());
     int64_t tiles = max_tiles(n, h->n_types);
     if (tiles > 0x7fffffffLL) return fail(BYSDF_ERR_INVALID_ARG, "too many tiles");
-    const bool mp4 = h->max_plies <= 4;
-    decltype(&k_backward<4, 0>) passes[3] = {mp4 ? k_backward<4, 0> : k_backward<8, 0>,
-                                             mp4 ? k_backward<4, 1> : k_backward<8, 1>,
-                                             mp4 ? k_backward<4, 2> : k_backward<8, 2>};
-    for (auto kern : passes) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(kBlock), 0, stream, h->d_types, h->d_tables, qp,
-                           type_offsets, h->n_types, tile_first, grad_E, partials, per_query);
-        HIP_TRY(hipGetLastError());
-    }
+    using Kernel = decltype(&k_backward<4, false, false>);
+    static constexpr Kernel kKernels[2][2][2] = {
+        {{k_backward<4, false, false>, k_backward<4, false, true>}, {k_backward<4, true, false>, k_backward<4, true, true>}},
+        {{k_backward<8, false, false>, k_backward<8, false, true>}, {k_backward<8, true, false>, k_backward<8, true, true>}}};
+    hipLaunchKernelGGL(kKernels[h->max_plies > 4][h->any_aniso][h->any_mig], dim3((unsigned)tiles), dim3(kBlock), 0,
+                       stream, h->d_types, h->d_tables, qp, type_offsets, h->n_types, tile_first, grad_E, partials,
+                       per_query);
+    HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(k_backward_sum, dim3((h->n_types + 255) / 256), dim3(256), 0, stream, tile_first,
                        h->n_types, partials, grad_theta);
     HIP_TRY(hipGetLastError());

@@ -284,9 +284,12 @@ template <class G, int MP> struct PlyHit {
 // unit yarn circle at offset h, then for each ply the fixed-point update of
 // the height at which the ply-centre helix crosses the ray's ellipse plane,
 // a 2D ray/disc test in the projected cross-section, and the closest ply.
+// dphase (nullable): the derivatives of the converged phases (radians) with
+// respect to the helix rate, times dwp (the adjoint's ply twist).
 template <class G, class S, int MP>
 __host__ __device__ inline void trace_plies(const Derived<G, S>& P, float h, float u, float v,
-                                            const V3<float>& wi, PlyHit<G, MP>& g)
+                                            const V3<float>& wi, PlyHit<G, MP>& g, G* dphase = nullptr,
+                                            double dwp = 0.0)
 {
     StageMark<G> mark(kStagePlies);
     g.pass = false;
@@ -322,11 +325,17 @@ __host__ __device__ inline void trace_plies(const Derived<G, S>& P, float h, flo
         G vj = vv;
         const G ck = G(P.ply_c[k]), sk = G(P.ply_s[k]);
         G c = c0 * ck - s0 * sk, s = s0 * ck + c0 * sk;
+        G dvj = G(0);
         for (int j = 0; j < P.N_it; ++j) {
             if (j > 0) sincos_turns_g(base + P.wp_turns * vj, &s, &c);
+            if (dphase) {
+                const G dth = G(kTwoPi) * (G(dwp) * vj + P.wp_turns * dvj);
+                dvj = g.kappa * P.Rpc * dth * (c * g.dhy - s * g.dhx);
+            }
             vj = vv + g.kappa * ((P.Rpc * c - g.x2x) * g.dhx + (P.Rpc * s - g.x2y) * g.dhy);
         }
         sincos_turns_g(base + P.wp_turns * vj, &s, &c);
+        if (dphase) dphase[k] = G(kTwoPi) * (G(dwp) * vj + P.wp_turns * dvj);
         g.cth[k] = c;
         g.sth[k] = s;
         G wx = g.x2x - P.Rpc * c, wy = g.x2y - P.Rpc * s;
@@ -382,10 +391,11 @@ __host__ __device__ inline int mig_table(uint32_t seed, int n_mig, int64_t q, in
 }
 
 // Periodic linear interpolation between the texel centres of the table at
-// texel offset base, at a phase given in turns.
+// texel offset base, at a phase given in turns; rate (nullable): the three
+// derivatives with respect to the phase.
 template <class G, class Tab>
 __host__ __device__ inline void table_at(const Tab& tab, int Nu, int base, const G& turns, G& dn, G& rh,
-                                         G& gf)
+                                         G& gf, G* rate = nullptr)
 {
     G fl = floor_g(turns);
     G x = (turns - fl) * G((double)Nu) - G(0.5);
@@ -401,7 +411,21 @@ __host__ __device__ inline void table_at(const Tab& tab, int Nu, int base, const
     dn = omf * G((double)t0.x) + f * G((double)t1.x);
     rh = omf * G((double)t0.y) + f * G((double)t1.y);
     gf = omf * G((double)t0.z) + f * G((double)t1.z);
+    if (rate) {
+        rate[0] = G((double)Nu) * (G((double)t1.x) - G((double)t0.x));
+        rate[1] = G((double)Nu) * (G((double)t1.y) - G((double)t0.y));
+        rate[2] = G((double)Nu) * (G((double)t1.z) - G((double)t0.z));
+    }
 }
+
+// What the reverse sweep over fiber_frame reads of the forward one.
+template <class G> struct FrameTape {
+    V3<G> tp, np, bp;          // ply frame
+    G sin_a, cos_a, kt, ks, rn;
+    G vply, rh, tfa, ca, sa, sdn, cdn, cs, q;
+    G rate[3];                 // d(dn, rh, gf) / d turns
+    G fade[3];                 // d(dn, rh, gf) / d vply through the blend of two tables
+};
 
 // Ply frame on the disc k with phase (cth, sth) at 2D outward normal (n2x,
 // n2y) and yarn height z, then the fiber frame from the 1D fiber table
@@ -413,7 +437,7 @@ __host__ __device__ inline void table_at(const Tab& tab, int Nu, int base, const
 template <class G, class S, class Tab>
 __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Tab& tab, G cth, G sth, int k,
                                                 G n2x, G n2y, G z, G* gf_out, G* cos_out,
-                                                G* sin_out)
+                                                G* sin_out, FrameTape<G>* tape = nullptr)
 {
     StageMark<G> mark(kStageFrame);
     // sine and cosine of the angle around the ply, (cth, sth) to (n2x, n2y)
@@ -439,14 +463,22 @@ __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Ta
         G w = (b > 0.0 && val(ph) > 1.0 - b) ? (ph - G(1.0 - b)) / G(b) : G(0);
         const int m0 = mig_table(P.mig_seed, P.n_mig, q, k), m1 = mig_table(P.mig_seed, P.n_mig, q + 1, k);
         G d0, r0, g0, d1, r1, g1;
-        table_at(tab, P.Nu, m0 * P.Nu, turns, d0, r0, g0);
-        table_at(tab, P.Nu, m1 * P.Nu, turns, d1, r1, g1);
+        G rate1[3];
+        table_at(tab, P.Nu, m0 * P.Nu, turns, d0, r0, g0, tape ? tape->rate : nullptr);
+        table_at(tab, P.Nu, m1 * P.Nu, turns, d1, r1, g1, tape ? rate1 : nullptr);
         G omw = G(1) - w;
+        if (tape) {
+            const G dw = val(w) > 0.0 ? G(1.0 / (b * P.mig_period)) : G(0);
+            tape->fade[0] = (d1 - d0) * dw;
+            tape->fade[1] = (r1 - r0) * dw;
+            tape->fade[2] = (g1 - g0) * dw;
+            for (int c = 0; c < 3; ++c) tape->rate[c] = omw * tape->rate[c] + w * rate1[c];
+        }
         dn = omw * d0 + w * d1;
         rh = omw * r0 + w * r1;
         gfv = omw * g0 + w * g1;
     } else {
-        table_at(tab, P.Nu, 0, turns, dn, rh, gfv);
+        table_at(tab, P.Nu, 0, turns, dn, rh, gfv, tape ? tape->rate : nullptr);
     }
     G sdn, cdn;
     sincos_turns_g(dn * G(kInvTwoPi), &sdn, &cdn);
@@ -460,6 +492,12 @@ __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Ta
     const G cs = ca * sdn, q = rsqrt_(cdn * cdn + cs * cs);
     fr.n = tp * (q * sa * cs) + np * (q * cdn) + bp * (q * ca * cs);
     fr.b = cross(fr.n, fr.t);
+    if (tape) {
+        tape->tp = tp; tape->np = np; tape->bp = bp;
+        tape->sin_a = sa_; tape->cos_a = ca_; tape->kt = kt; tape->ks = ks; tape->rn = rn;
+        tape->vply = vply; tape->rh = rh; tape->tfa = tfa; tape->ca = ca; tape->sa = sa;
+        tape->sdn = sdn; tape->cdn = cdn; tape->cs = cs; tape->q = q;
+    }
     if (gf_out) *gf_out = gfv;
     if (cos_out) {
         *cos_out = ca_;
@@ -469,6 +507,11 @@ __host__ __device__ inline Frame<G> fiber_frame(const Derived<G, S>& P, const Ta
 }
 
 // ---------------------------------------------------------------- shadowing
+
+// One of two values.  A conditional expression of two variables of a class
+// type selects between their addresses and keeps both in memory.
+__host__ __device__ inline double pick(bool c, double a, double b) { return c ? a : b; }
+template <class G> __host__ __device__ inline G pick(bool c, G a, G b) { return c ? a : b; }
 
 // Raw ply visibility (Sec. 4.1.4): at the angle with cosine and sine (na_x,
 // na_y) around ply 0 of the nominal cross-section, the share of the window [phi - dP, phi + dP] of incident
@@ -505,11 +548,11 @@ __host__ __device__ inline G ply_shadow_raw(int Np, G rp, G Rpc, G dP, G na_x, G
         // copy of the set closest to the window
         G shift = G(kTwoPi * rint(val((cen - phi) * G(kInvTwoPi))));
         G l = cen - half - shift, h2 = cen + half - shift;
-        l = val(l) > val(wlo) ? l : wlo;
-        h2 = val(h2) < val(whi) ? h2 : whi;
+        l = pick(val(l) > val(wlo), l, wlo);
+        h2 = pick(val(h2) < val(whi), h2, whi);
         bool ok = live && val(h2) > val(l);
-        lo[s] = ok ? l : big;
-        hi[s] = ok ? h2 : big;
+        lo[s] = pick(ok, l, big);
+        hi[s] = pick(ok, h2, big);
     }
     // sort by lower end (odd-even transposition network, MP passes)
 #pragma unroll
@@ -517,8 +560,8 @@ __host__ __device__ inline G ply_shadow_raw(int Np, G rp, G Rpc, G dP, G na_x, G
 #pragma unroll
         for (int i = pass & 1; i + 1 < MP; i += 2) {
             bool sw = val(lo[i + 1]) < val(lo[i]);
-            G a0 = sw ? lo[i + 1] : lo[i], a1 = sw ? lo[i] : lo[i + 1];
-            G b0 = sw ? hi[i + 1] : hi[i], b1 = sw ? hi[i] : hi[i + 1];
+            G a0 = pick(sw, lo[i + 1], lo[i]), a1 = pick(sw, lo[i], lo[i + 1]);
+            G b0 = pick(sw, hi[i + 1], hi[i]), b1 = pick(sw, hi[i], hi[i + 1]);
             lo[i] = a0; lo[i + 1] = a1; hi[i] = b0; hi[i + 1] = b1;
         }
     }

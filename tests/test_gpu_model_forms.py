@@ -1,0 +1,103 @@
+"""The model's forms at the edges of their rules: the exit refraction's
+scalar form (isotropic roughness, index at least 1.25) and vector form on
+either side of the line, and the adjoint's kernels over plies, nodes,
+anisotropy, migration and lattice shifts.
+
+Evaluation against the FP64 oracle under the parity rule; the adjoint against
+the oracle's central differences with the tolerance and the exclusions of
+the other adjoint tests.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2401_12724_amd import bysdf, workloads as W
+from parity import assert_parity, compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch
+
+
+# 1.25 is a single-precision value; its neighbours are one ulp away
+_BELOW, _ABOVE = float(np.nextafter(np.float32(1.25), np.float32(1))), float(np.nextafter(np.float32(1.25), np.float32(2)))
+
+
+@pytest.mark.parametrize("eta,aniso", [(1.05, 1.0), (_BELOW, 1.0), (1.25, 1.0), (_ABOVE, 1.0), (2.4, 1.0),
+                                       (1.25, 1.6), (1.25, float(np.nextafter(np.float32(1), np.float32(2))))])
+def test_exit_refraction_forms(torch_cuda, eta, aniso):
+    torch = torch_cuda
+    P = [W.default_params(eta=eta, aniso=aniso)]
+    n = 8192 + 37
+    q = W.queries(n, 91, n_types=1, v_max=20.0)
+    T = bysdf.bysdf_types_create(P)
+    ev, fl = bysdf.bysdf_eval(T, bysdf.to_device(q))
+    torch.cuda.synchronize()
+    o, of = oracle.eval(P, q)
+    assert_parity(compare(ev.cpu().numpy().T, fl.cpu().numpy(), o[:, :12], of), max_flagged=0.05)
+
+
+@pytest.mark.parametrize("plies,nodes,aniso,eta,mig,shift", [
+    (1, 1, 1.0, 1.55, 1, False),
+    (4, 16, 1.0, 1.2, 1, True),
+    (5, 4, 1.0, 1.55, 1, False),
+    (8, 3, 0.6, 1.3, 1, True),
+    (3, 4, 1.8, 1.55, 1, False),
+    (3, 4, 1.8, 1.55, 4, False),
+    (6, 2, 1.0, 1.7, 4, True),
+])
+def test_adjoint_forms(torch_cuda, plies, nodes, aniso, eta, mig, shift):
+    """Two types of one form, the second isotropic, 300 queries each (a full
+    tile and a remainder)."""
+    torch = torch_cuda
+    rp = W.packed_ply_radius(plies)
+    base = dict(n_plies=plies, ply_radius=rp, ply_center_radius=1 - rp if plies > 1 else 0.0, K=nodes, eta=eta,
+                ply_density=0.8, fiber_density=0.7, B=0.5, r=0.6)
+    if mig > 1:
+        base.update(mig_tables=mig, mig_period=4.0, mig_blend=0.3, mig_spread=0.3)
+    P = [W.default_params(aniso=aniso, **base), W.default_params(beta=0.25, **base)]
+    per = 300
+    tid = np.repeat(np.arange(2, dtype=np.int32), per)
+    q = W.queries(2 * per, 17 + plies, type_ids=tid, v_max=10.0)
+    off = np.array([0, per, 2 * per], dtype=np.int64)
+    gE = np.random.default_rng(6).normal(size=(2 * per, 3)).astype(np.float32)
+    ts = oracle.TypeSet(P)
+    _, a = oracle.grad_fd(ts, q, gE, 1e-7)
+    _, b = oracle.grad_fd(ts, q, gE, 3e-8)
+    _, fl = oracle.eval(ts, q)
+    ok = np.all(np.abs(a - b) <= 1e-4 * np.maximum(np.abs(a), 1e-7) + 1e-9, axis=1)
+    ok &= (fl & oracle.MARGIN_MASK) == 0
+    assert ok.mean() > 0.85, ok.mean()
+    T = bysdf.bysdf_types_create(P)
+    if shift:  # the differences have no shift: a shift of zero is the same lattice
+        q["shift"] = np.zeros((2, 2 * per), np.float32)
+    g, pq = bysdf.bysdf_eval_backward(T, bysdf.to_device(q), torch.from_numpy(off).cuda(),
+                                      torch.from_numpy(gE).cuda(), per_query=True)
+    torch.cuda.synchronize()
+    pq, g = pq.cpu().numpy(), g.cpu().numpy()
+    tol = 1e-3 * np.abs(a) + 1e-6 * np.abs(a).max(0)
+    bad = (np.abs(pq - a) > tol) & ok[:, None]
+    print("per-query bad", bad.sum(0), "of", ok.sum())
+    assert not bad.any()
+    # a type's sum over its tiles
+    ref = pq.astype(np.float64).reshape(2, per, 8)
+    assert np.all(np.abs(g - ref.sum(1)) <= 300 * 2.0 ** -24 * np.abs(ref).sum(1))
+    if shift:
+        # the albedo's derivative is the body lobes at unit albedo, which the
+        # shift moves: against the evaluation on the same queries (sums of up
+        # to 17 single-precision terms, formed in another order)
+        q["shift"] = np.random.default_rng(5).random((2, 2 * per)).astype(np.float32)
+        qd = bysdf.to_device(q)
+        _, pq = bysdf.bysdf_eval_backward(T, qd, torch.from_numpy(off).cuda(), torch.from_numpy(gE).cuda(),
+                                          per_query=True)
+        ev, _ = bysdf.bysdf_eval(T, qd)
+        torch.cuda.synchronize()
+        ev, pq = ev.cpu().numpy().T, pq.cpu().numpy()
+        want = gE * (ev[:, 5:8] + ev[:, 8:11])
+        got = pq[:, :3] * np.float32(P[0]["albedo"])
+        assert np.all(np.abs(got - want) <= 1e-5 * np.abs(want) + 1e-7)
