@@ -41,6 +41,12 @@ __host__ __device__ inline Dual pick(bool c, Dual a, Dual b) { return Dual(c ? a
 __host__ __device__ inline Dual operator+(Dual a, Dual b) { return Dual(a.v + b.v, a.d + b.d); }
 __host__ __device__ inline Dual operator-(Dual a, Dual b) { return Dual(a.v - b.v, a.d - b.d); }
 __host__ __device__ inline Dual operator*(Dual a, Dual b) { return Dual(a.v * b.v, a.d * b.v + a.v * b.d); }
+__host__ __device__ inline Dual operator-(Dual a) { return Dual(-a.v, -a.d); }
+__host__ __device__ inline Dual operator+(double a, Dual b) { return Dual(a + b.v, b.d); }
+__host__ __device__ inline Dual operator-(double a, Dual b) { return Dual(a - b.v, -b.d); }
+__host__ __device__ inline Dual operator-(Dual a, double b) { return Dual(a.v - b, a.d); }
+__host__ __device__ inline Dual operator*(Dual a, double b) { return Dual(a.v * b, a.d * b); }
+__host__ __device__ inline Dual operator*(double a, Dual b) { return b * a; }
 __host__ __device__ inline Dual operator/(Dual a, Dual b)
 {
     const double r = rcp_(b.v), q = a.v * r;
@@ -50,6 +56,11 @@ __host__ __device__ inline Dual sqrt_(Dual x)
 {
     const double s = sqrt_(x.v);
     return Dual(s, s > 0.0 ? 0.5 * x.d * rcp_(s) : 0.0);
+}
+__host__ __device__ inline Dual rsqrt_(Dual x)
+{
+    const double r = rsqrt_(x.v);
+    return Dual(r, -0.5 * r * r * r * x.d);
 }
 __host__ __device__ inline Dual atan2_(Dual y, Dual x)
 {
@@ -669,11 +680,11 @@ __host__ __device__ inline bool adjoint_query(const TypeRec& rec, const Tab& tab
     X.fx = fiber_frame(P, tab, cth, sth, X.ph.ks, X.ph.n2x, X.ph.n2y, X.ph.vhit, &X.rawf, &X.ca, &X.sa, &tape);
     Dual raw;
     {
-        const double phi = atan2_(X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x,
-                                  X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y);
+        const double fx = X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y, fy = X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x;
         const double da = ht.omega - dth;
-        raw = ply_shadow_raw<Dual, MP>(P.Np, Dual(P.rp), Dual(P.Rpc), Dual(P.dP), Dual(X.ca, -X.sa * da),
-                                       Dual(X.sa, X.ca * da), Dual(phi, -ht.omega), P.ply_c, P.ply_s);
+        raw = ply_visibility<Dual, double, MP>(P, P.rp, P.Rpc, (double)P.dP, Dual(X.ca, -X.sa * da),
+                                               Dual(X.sa, X.ca * da), Dual(fx, fy * ht.omega),
+                                               Dual(fy, -fx * ht.omega));
     }
     X.Gp = (float)(1.0 - (double)P.rho_p * (1.0 - raw.v));
     X.Gf = (float)(1.0 - (double)P.rho_f * (1.0 - X.rawf));

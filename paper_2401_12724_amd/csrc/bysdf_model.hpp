@@ -65,6 +65,10 @@ template <class G, class S> struct Derived {
     // directions of the ply centres of the nominal cross-section,
     // (cos, sin)(2 pi k / N_p), k < N_p
     double ply_c[kMaxPlies], ply_s[kMaxPlies];
+    // the visibility window: cosine and sine of its half width, 1 / its
+    // width, and whether it is narrow (see ply_visibility_narrow)
+    double win_c, win_s, win_i;
+    int win_narrow;
 };
 
 // Per-type record resident in device memory: the primary parameters and
@@ -124,6 +128,15 @@ __host__ __device__ inline void fill_derived(TypeRec& t)
         d.ply_s[k] = 0.0;
         if (k < t.n_plies) sincos_turns(k * d.inv_np, &d.ply_s[k], &d.ply_c[k]);
     }
+    const double dP = (double)t.shadow_hw;
+    d.win_c = cos(dP);
+    d.win_s = sin(dP);
+    d.win_i = 0.5 / dP;
+    // farthest another ply's centre lies from a point of a ply's rim
+    double far = 0.0;
+    for (int k = 1; k < t.n_plies; ++k) far = fmax(far, sqrt(fmax(2.0 - 2.0 * d.ply_c[k], 0.0)));
+    far = far * t.Rpc + t.rp;
+    d.win_narrow = dP <= 0.25 * kPi && d.win_s * far < 0.999 * t.rp;
 }
 
 __host__ __device__ inline Derived<double, float> derive(const TypeRec& t) { return t.d; }
@@ -147,6 +160,7 @@ template <class G2, class S2> inline Derived<G2, S2> rebind(const Derived<double
         d.ply_c[k] = f.ply_c[k];
         d.ply_s[k] = f.ply_s[k];
     }
+    d.win_c = f.win_c; d.win_s = f.win_s; d.win_i = f.win_i; d.win_narrow = f.win_narrow;
     return d;
 }
 
@@ -583,6 +597,75 @@ __host__ __device__ inline G ply_shadow_raw(int Np, G rp, G Rpc, G dP, G na_x, G
     return val(vis) < 0.0 ? G(0) : (val(vis) > 1.0 ? G(1) : vis);
 }
 
+// The same share for a narrow window: at most a quarter turn wide and
+// narrower than any ply's disc seen from another's rim, so a set that meets
+// it covers one of its edges.  What stays visible is then one piece, between
+// the farthest end of the sets over the lower edge and the nearest of those
+// over the upper edge, and all comparisons are signs of products of the
+// directions: one arctangent, of the angle between the two ends, against one
+// for the window and two per ply, and no sorting.  (f_x, f_y): cosine and
+// sine of the window's centre phi, of any common length.  2^24
+// queries of 1,024 types: 2.74 -> 2.53 ms.
+template <class G, class C, int MP>
+__host__ __device__ inline G ply_visibility_narrow(int Np, C rp, C Rpc, C wc, C ws, C wi, G na_x, G na_y, G f_x, G f_y,
+                                                   const double* ply_c, const double* ply_s)
+{
+    const G il = rsqrt_(f_x * f_x + f_y * f_y), c = f_x * il, s = f_y * il;
+    // the window's edges, lower a and upper b
+    const G Fx = c * na_x - s * na_y, Fy = c * na_y + s * na_x;
+    G ax = Fx * wc + Fy * ws, ay = Fy * wc - Fx * ws;
+    G bx = Fx * wc - Fy * ws, by = Fy * wc + Fx * ws;
+    const G Lx = ax, Ly = ay, Ux = bx, Uy = by;
+    // the ply itself: directions below its tangent line
+    const G cc = c * wc, sc = s * ws;
+    bool cl = val(cc) + val(sc) < 0.0, cu = val(cc) - val(sc) < 0.0;
+    bool full = cl && cu, any = cl || cu;
+    const G Px = Rpc + rp * na_x, Py = rp * na_y;
+    ax = pick(cl, na_y, ax);
+    ay = pick(cl, -na_x, ay);
+    bx = pick(cu, -na_y, bx);
+    by = pick(cu, na_x, by);
+#pragma unroll
+    for (int k = 1; k < MP; ++k) {
+        if (k >= Np) break;
+        const G wx = Rpc * C(ply_c[k]) - Px, wy = Rpc * C(ply_s[k]) - Py;
+        // |w| times the cosine of the half width; a point inside the disc
+        // sees a half turn of it
+        const G e2 = wx * wx + wy * wy - rp * rp;
+        const G r = sqrt_(pick(val(e2) > 0.0, e2, G(0)));
+        cl = val(wx * Lx + wy * Ly) > val(r);
+        cu = val(wx * Ux + wy * Uy) > val(r);
+        full = full || (cl && cu);
+        any = any || cl || cu;
+        const G hx = wx * r - wy * rp, hy = wy * r + wx * rp;
+        const G lx = wx * r + wy * rp, ly = wy * r - wx * rp;
+        cl = cl && val(ax * hy - ay * hx) > 0.0;
+        cu = cu && val(lx * by - ly * bx) > 0.0;
+        ax = pick(cl, hx, ax);
+        ay = pick(cl, hy, ay);
+        bx = pick(cu, lx, bx);
+        by = pick(cu, ly, by);
+    }
+    const G cr = ax * by - ay * bx;
+    if (full || val(cr) <= 0.0) return G(0);
+    if (!any) return G(1);
+    const G vis = atan2_(cr, ax * bx + ay * by) * wi;
+    return val(vis) > 1.0 ? G(1) : vis;
+}
+
+// Visibility at x from the angle around the ply (na_x, na_y) and the
+// incident direction in the ply hit's frame, (cosine, sine) of phi times any
+// length: the narrow form for the types that allow it (settled by the
+// record, so a wavefront that serves one type takes one branch).
+template <class G, class C, int MP, class P>
+__host__ __device__ inline G ply_visibility(const P& D, C rp, C Rpc, C dP, G na_x, G na_y, G f_x, G f_y)
+{
+    if (D.win_narrow)
+        return ply_visibility_narrow<G, C, MP>(D.Np, rp, Rpc, C(D.win_c), C(D.win_s), C(D.win_i), na_x, na_y, f_x, f_y,
+                                               D.ply_c, D.ply_s);
+    return ply_shadow_raw<G, MP>(D.Np, G(rp), G(Rpc), G(dP), na_x, na_y, atan2_(f_y, f_x), D.ply_c, D.ply_s);
+}
+
 // ---------------------------------------------------------------- state at x
 
 template <class G, class S, int MP> struct XState {
@@ -636,8 +719,9 @@ __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const 
     G raw;
     {
         StageMark<G> mark(kStageShadow);
-        G phi = atan2_(X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x, X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y);
-        raw = ply_shadow_raw<G, MP>(P.Np, P.rp, P.Rpc, G(val(P.dP)), X.ca, X.sa, phi, P.ply_c, P.ply_s);
+        raw = ply_visibility<G, G, MP>(P, P.rp, P.Rpc, G(val(P.dP)), X.ca, X.sa,
+                                       X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y,
+                                       X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x);
     }
     X.rawp = raw;
     X.rawf = gft;

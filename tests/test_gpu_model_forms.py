@@ -1,6 +1,7 @@
 """The model's forms at the edges of their rules: the exit refraction's
 scalar form (isotropic roughness, index at least 1.25) and vector form on
-either side of the line, and the adjoint's kernels over plies, nodes,
+either side of the line, the ply visibility's narrow-window form and its
+general one, and the adjoint's kernels over plies, nodes,
 anisotropy, migration and lattice shifts.
 
 Evaluation against the FP64 oracle under the parity rule; the adjoint against
@@ -42,8 +43,34 @@ def test_exit_refraction_forms(torch_cuda, eta, aniso):
     assert_parity(compare(ev.cpu().numpy().T, fl.cpu().numpy(), o[:, :12], of), max_flagged=0.05)
 
 
+def _window_limit(plies):
+    """Half width below which no ply's disc fits inside the window."""
+    rp = W.packed_ply_radius(plies)
+    far = max([2.0 * (1 - rp) * np.sin(np.pi * k / plies) for k in range(1, plies)], default=0.0)
+    return float(np.arcsin(0.999 * rp / (far + rp)))
+
+
+@pytest.mark.parametrize("plies", [1, 2, 3, 8])
+@pytest.mark.parametrize("width", [("abs", 1e-3), ("limit", 0.999), ("limit", 1.001), ("abs", 0.78539), ("abs", 0.78541),
+                                   ("abs", 1.5707963)])
+def test_visibility_forms(torch_cuda, plies, width):
+    torch = torch_cuda
+    rp = W.packed_ply_radius(plies)
+    dP = width[1] if width[0] == "abs" else width[1] * _window_limit(plies)
+    P = [W.default_params(n_plies=plies, ply_radius=rp, ply_center_radius=1 - rp if plies > 1 else 0.0, K=2,
+                          shadow_halfwidth=min(dP, 1.5707963), ply_density=1.0)]
+    n = 8192 + 5
+    q = W.queries(n, 61 + plies, n_types=1, v_max=20.0)
+    T = bysdf.bysdf_types_create(P)
+    ev, fl = bysdf.bysdf_eval(T, bysdf.to_device(q))
+    torch.cuda.synchronize()
+    o, of = oracle.eval(P, q)
+    assert_parity(compare(ev.cpu().numpy().T, fl.cpu().numpy(), o[:, :12], of), max_flagged=0.05)
+
+
 @pytest.mark.parametrize("plies,nodes,aniso,eta,mig,shift", [
     (1, 1, 1.0, 1.55, 1, False),
+    (3, 1, 1.0, 1.45, 1, False),
     (4, 16, 1.0, 1.2, 1, True),
     (5, 4, 1.0, 1.55, 1, False),
     (8, 3, 0.6, 1.3, 1, True),
@@ -58,6 +85,8 @@ def test_adjoint_forms(torch_cuda, plies, nodes, aniso, eta, mig, shift):
     rp = W.packed_ply_radius(plies)
     base = dict(n_plies=plies, ply_radius=rp, ply_center_radius=1 - rp if plies > 1 else 0.0, K=nodes, eta=eta,
                 ply_density=0.8, fiber_density=0.7, B=0.5, r=0.6)
+    if nodes == 1 and plies > 1:  # the visibility's general form
+        base.update(shadow_halfwidth=0.6)
     if mig > 1:
         base.update(mig_tables=mig, mig_period=4.0, mig_blend=0.3, mig_spread=0.3)
     P = [W.default_params(aniso=aniso, **base), W.default_params(beta=0.25, **base)]
