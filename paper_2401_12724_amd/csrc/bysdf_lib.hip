@@ -1018,7 +1018,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
             tab.p = kLds ? s_tab : tables + R.table_off;
             const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, f);
             XState<double, float, MP> X;
-            state_at_x(Pm, tab, stratum_h(f, s), m.u, m.v, m.wi, X);
+            bysdf::state_at_x_of<false>(Pm, tab, stratum_h(f, s), m.u, m.v, m.wi, X);
             if (single) fl |= X.ph.flags & ~F_PASS_THROUGH;
             pass = X.ph.pass;
             if (pass) return;
@@ -1064,7 +1064,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
                 const float hj = stratum_h(fo, j);
                 XState<double, float, MP> X;
-                state_at_x(Pm, tab, hj, mo.u, mo.v, mo.wi, X);
+                bysdf::state_at_x_of<false>(Pm, tab, hj, mo.u, mo.v, mo.wi, X);
                 if (X.ph.pass) return;
                 if (!single_o) {
                     Frame<double> Fo;
