@@ -298,9 +298,9 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 // scalar registers; the 25 to 40 pointers of the query kernels fill those
 // through the whole body, and the type's scalars and the polynomials'
 // constants spill for them.  Scratch per lane falls from 104 to 80 B in
-// k_eval_sample, 96 to 28 B in k_eval, 300 to 156 B in k_eval_multi; eval and
-// sample of 4 Mi queries 3314 -> 3222 us, 262144 footprint queries
-// 455 -> 430 us.  The two pointers stay ordinary `__restrict__` parameters:
+// k_eval_sample and 96 to 28 B in k_eval; eval and sample of 2^24 queries
+// 3314 -> 3222 us.  The multi-scale kernels take their arguments in the
+// ordinary way: see load_mquery.  The two pointers stay ordinary `__restrict__` parameters:
 // through a struct the type records would be loaded by the vector unit.
 template <class A> __device__ inline A late_args()
 {
@@ -619,11 +619,9 @@ struct MQuery {
     float h, u, v, h1, h2, zeta;
     V3<float> wi;
 };
-template <class A> __device__ inline MQuery load_mquery(int64_t i)
+template <class QP>
+__device__ inline MQuery load_mquery(const QP& q, const FPtrs& fp, int64_t i)
 {
-    const A in = late_args<A>();
-    const auto& q = in.q;
-    const FPtrs& fp = in.fp;
     MQuery m;
     m.h = q.h[i];
     m.u = q.u[i];
@@ -639,10 +637,11 @@ template <class A> __device__ inline MQuery load_mquery(int64_t i)
 // return each lane holds its footprint's frame and shadowing, as
 // footprint_geometry computes them; `any` is false when no stratum of
 // positive weight hits a ply.
-template <bool kLds, int MP, bool MIG, class A>
+template <bool kLds, int MP, bool MIG, class QP>
 __device__ inline void wave_footprint_geometry(const TypeRec* __restrict__ types,
                                                const float4* __restrict__ tables, const float4* s_tab,
-                                               int n_max, int64_t b, int t, int first, int nq, int S, Frame<double>& F,
+                                               const QP& q, const FPtrs& fp, int n_max, int64_t b,
+                                               int t, int first, int nq, int S, Frame<double>& F,
                                                float& Gm, bool& any, uint32_t& fl)
 {
     V3<double> sn = mk3<double>(0.0, 0.0, 0.0), st = sn, n0 = sn, t0 = sn;
@@ -661,7 +660,7 @@ __device__ inline void wave_footprint_geometry(const TypeRec* __restrict__ types
             const TypeRec& R = types[tu];
             TabPtrT<MIG> tab;
             tab.p = kLds ? s_tab : tables + R.table_off;
-            const MQuery m = load_mquery<A>(b + own);
+            const MQuery m = load_mquery(q, fp, b + own);
             Footprint fo;
             make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, fo);
             const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
@@ -748,45 +747,34 @@ struct MultiSampleLds {
     int lobe[kWave], node[kWave];
 };
 
-struct EvalMultiArgs {
-    int n_types, lds_texels, n_max, unused;
-    QPtrs q;
-    FPtrs fp;
-    OPtrs o;
-    int64_t n;
-};
-
 template <bool kLds, int MP, bool MIG>
 __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
-    const TypeRec* __restrict__ types, const float4* __restrict__ tables, EvalMultiArgs args)
+    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
+    QPtrs q, FPtrs fp, int n_max, OPtrs o, int64_t n)
 {
-    using A = EvalMultiArgs;
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     __shared__ MultiLds s_ml[kBlock / kWave];
     if (kLds) {
-        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int lane = __lane_id();
     MultiLds& L = s_ml[threadIdx.x / kWave];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     // whole wavefronts iterate together (the cross-lane steps need every lane)
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < late_args<A>().n; b += stride) {
-        const int n_max = late_args<A>().n_max;
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < n; b += stride) {
         const int64_t i = b + lane;
-        const bool in = i < late_args<A>().n;
-        const int t = in ? late_args<A>().q.type[i] : 0;
+        const bool in = i < n;
+        const int t = in ? q.type[i] : 0;
         uint32_t fl = F_BAD_INPUT;
         double wsum = 1.0;
         int nq = 0;
         if (in) {
-            const MQuery m = load_mquery<A>(i);
-            const A in_args = late_args<A>();
-            const QPtrs& q = in_args.q;
+            const MQuery m = load_mquery(q, fp, i);
             const V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
-            fl = (t < 0 || t >= in_args.n_types) ? F_BAD_INPUT : 0u;
+            fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
             fl |= check_inputs(m.h, m.u, m.v, m.wi) | check_dir(wo) | check_footprint(m.h, m.h1, m.h2, m.zeta);
             if (fl == 0u) {
                 Footprint f;
@@ -807,7 +795,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
             Frame<double> F;
             float Gm;
             bool any;
-            wave_footprint_geometry<kLds, MP, MIG, A>(types, tables, s_tab, n_max, b, t, firsta, nqa, Sa,
+            wave_footprint_geometry<kLds, MP, MIG>(types, tables, s_tab, q, fp, n_max, b, t, firsta, nqa, Sa,
                                                    F, Gm, any, fl);
             if (nqa > 0 && !any) fl |= F_PASS_THROUGH;
             wave_lds_sync();
@@ -837,7 +825,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
                 TabPtrT<MIG> tab;
                 tab.p = kLds ? s_tab : tables + R.table_off;
                 const int64_t io = b + own;
-                const MQuery m = load_mquery<A>(io);
+                const MQuery m = load_mquery(q, fp, io);
                 Footprint fo;
                 make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, fo);
                 const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
@@ -855,8 +843,6 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
                     apply_aggregate(Pm, X, Fo, L.gm[own]);
                 }
                 back = !(X.mu_i > 0.0f);
-                const A in_args = late_args<A>();
-                const QPtrs& q = in_args.q;
                 const float s0 = q.s0 ? q.s0[io] : 0.0f, s1 = q.s1 ? q.s1[io] : 0.0f;
                 const V3<double> wo_g = mk3<double>(q.wox[io], q.woy[io], q.woz[io]);
                 EvalOut<float> e;
@@ -898,8 +884,6 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
         if (!in) continue;
         if (single && !hit1) fl |= F_PASS_THROUGH;
         const float iw = float(1.0 / wsum);
-        const A out = late_args<A>();
-        const OPtrs& o = out.o;
         o.Er[i] = L.acc[0][lane] * iw; o.Eg[i] = L.acc[1][lane] * iw; o.Eb[i] = L.acc[2][lane] * iw;
         o.ExS[i] = L.acc[3][lane] * iw; o.EyS[i] = L.acc[4][lane] * iw;
         o.ExBr[i] = L.acc[5][lane] * iw; o.ExBg[i] = L.acc[6][lane] * iw; o.ExBb[i] = L.acc[7][lane] * iw;
@@ -909,38 +893,29 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_eval_multi(
     }
 }
 
-struct SampleMultiArgs {
-    int n_types, lds_texels, n_max, unused;
-    SPtrs q;
-    FPtrs fp;
-    SOPtrs o;
-    int64_t n;
-};
-
 // OWNXI: the uniforms come from the generator (xi arrays NULL).  Only the
 // instance that needs it carries the generator: its code alone, never run,
 // costs the multi-scale sampler a quarter of its speed in registers.
 template <bool kLds, int MP, bool MIG, bool OWNXI>
 __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
-    const TypeRec* __restrict__ types, const float4* __restrict__ tables, SampleMultiArgs args)
+    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
+    SPtrs q, FPtrs fp, int n_max, SOPtrs o, int64_t n)
 {
-    using A = SampleMultiArgs;
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     __shared__ MultiSampleLds s_ml[kBlock / kWave];
     if (kLds) {
-        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int lane = __lane_id();
     MultiSampleLds& L = s_ml[threadIdx.x / kWave];
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < late_args<A>().n; b += stride) {
-        const int n_max = late_args<A>().n_max;
+    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); b < n; b += stride) {
         const int64_t i = b + lane;
-        const bool in = i < late_args<A>().n;
-        int t = in ? late_args<A>().q.type[i] : 0;
+        const bool in = i < n;
+        int t = in ? q.type[i] : 0;
         uint32_t fl = F_BAD_INPUT;
         Footprint f;
         f.n = 0;
@@ -948,10 +923,8 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
         MQuery m{};
         float xs = 0.0f, x0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
         if (in) {
-            m = load_mquery<A>(i);
-            const A in_args = late_args<A>();
-            const SPtrs& q = in_args.q;
-            xs = in_args.fp.xi_s[i];
+            m = load_mquery(q, fp, i);
+            xs = fp.xi_s[i];
             if (OWNXI) {
                 query_xi(q, i, x0, x1, x2);
             } else {
@@ -959,7 +932,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 x1 = q.xi1[i];
                 x2 = q.xi2[i];
             }
-            fl = (t < 0 || t >= in_args.n_types) ? F_BAD_INPUT : 0u;
+            fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
             fl |= check_inputs(m.h, m.u, m.v, m.wi) | check_footprint(m.h, m.h1, m.h2, m.zeta);
             if (!(xs >= 0.0f && xs < 1.0f)) fl |= F_BAD_INPUT;
             if (fl == 0u) make_footprint(m.h, m.h1, m.h2, m.zeta, n_max, f);
@@ -976,7 +949,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
         {
             Frame<double> F;
             float Gm;
-            wave_footprint_geometry<kLds, MP, MIG, A>(types, tables, s_tab, n_max, b, t, firsta, nqa, Sa,
+            wave_footprint_geometry<kLds, MP, MIG>(types, tables, s_tab, q, fp, n_max, b, t, firsta, nqa, Sa,
                                                    F, Gm, any, fl);
             wave_lds_sync();
             L.fn[0][lane] = F.n.x; L.fn[1][lane] = F.n.y; L.fn[2][lane] = F.n.z;
@@ -1004,21 +977,14 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
             }
         }
         bool drawn = false, pass = good && !any && !single;
-        bool has_shift;
-        float s0, s1;
-        {
-            const A in_args = late_args<A>();
-            has_shift = in_args.q.s0 != nullptr;
-            s0 = in && has_shift ? in_args.q.s0[i] : 0.0f;
-            s1 = in && has_shift ? in_args.q.s1[i] : 0.0f;
-        }
+        const float s0 = in && q.s0 ? q.s0[i] : 0.0f, s1 = in && q.s1 ? q.s1[i] : 0.0f;
         for_each_wave_type<false>(t, good && (any || single), [&](int tu) {
             const TypeRec& R = types[tu];
             TabPtrT<MIG> tab;
             tab.p = kLds ? s_tab : tables + R.table_off;
             const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, f);
             XState<double, float, MP> X;
-            bysdf::state_at_x_of<false>(Pm, tab, stratum_h(f, s), m.u, m.v, m.wi, X);
+            state_at_x(Pm, tab, stratum_h(f, s), m.u, m.v, m.wi, X);
             if (single) fl |= X.ph.flags & ~F_PASS_THROUGH;
             pass = X.ph.pass;
             if (pass) return;
@@ -1029,7 +995,7 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 Fo.b = cross(Fo.n, Fo.t);
                 apply_aggregate(Pm, X, Fo, L.gm[lane]);
             }
-            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{Pm, tab, X, s0, s1, has_shift};
+            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{Pm, tab, X, s0, s1, q.s0 != nullptr};
             SampleOut<float> so;
             V3<double> wo;
             fl |= sample_draw(Pm, X, m.wi, x0, x1, x2, nf, so, wo, drawn);
@@ -1058,13 +1024,13 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                 TabPtrT<MIG> tab;
                 tab.p = kLds ? s_tab : tables + R.table_off;
                 const int64_t io = b + own;
-                const MQuery mo = load_mquery<A>(io);
+                const MQuery mo = load_mquery(q, fp, io);
                 Footprint fo;
                 make_footprint(mo.h, mo.h1, mo.h2, mo.zeta, n_max, fo);
                 const Derived<double, float> Pm = widened(R.d, R.beta, R.aniso, fo);
                 const float hj = stratum_h(fo, j);
                 XState<double, float, MP> X;
-                bysdf::state_at_x_of<false>(Pm, tab, hj, mo.u, mo.v, mo.wi, X);
+                state_at_x(Pm, tab, hj, mo.u, mo.v, mo.wi, X);
                 if (X.ph.pass) return;
                 if (!single_o) {
                     Frame<double> Fo;
@@ -1073,8 +1039,6 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
                     Fo.b = cross(Fo.n, Fo.t);
                     apply_aggregate(Pm, X, Fo, L.gm[own]);
                 }
-                const A in_args = late_args<A>();
-                const SPtrs& q = in_args.q;
                 const float t0 = q.s0 ? q.s0[io] : 0.0f, t1 = q.s1 ? q.s1[io] : 0.0f;
                 const V3<double> wd = mk3<double>(L.wo[0][own], L.wo[1][own], L.wo[2][own]);
                 EvalOut<float> e;
@@ -1098,9 +1062,6 @@ __global__ __launch_bounds__(kBlock, BYSDF_MULTI_MIN_WAVES) void k_sample_multi(
             }
         }
         if (!in) continue;
-        const A out = late_args<A>();
-        const SPtrs& q = out.q;
-        const SOPtrs& o = out.o;
         SampleOut<float> so;
         for (int c = 0; c < 3; ++c) {
             so.wo[c] = so.wgt[c] = 0.0f;
@@ -2009,8 +1970,8 @@ extern "C" int bysdf_eval_multi(const bysdf_types_t* h, const bysdf_query_soa* q
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval_multi, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
-                       EvalMultiArgs{h->n_types, tx, n_max, 0, qp, fpp, op, n});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
+                       h->d_tables, tx, qp, fpp, (int)n_max, op, n);
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -2049,8 +2010,8 @@ extern "C" int bysdf_sample_multi(const bysdf_types_t* h, const bysdf_sample_soa
                                                         : k_sample_multi<false, 8, false, X>)))
     auto kern = q->xi0 ? BYSDF_PICK_SM(false) : BYSDF_PICK_SM(true);
 #undef BYSDF_PICK_SM
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
-                       SampleMultiArgs{h->n_types, tx, n_max, 0, sp, fpp, op, n});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
+                       h->d_tables, tx, sp, fpp, (int)n_max, op, n);
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
