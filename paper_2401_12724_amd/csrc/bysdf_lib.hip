@@ -300,7 +300,8 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 // constants spill for them.  Scratch per lane falls from 104 to 80 B in
 // k_eval_sample and 96 to 28 B in k_eval; eval and sample of 2^24 queries
 // 3314 -> 3222 us.  The multi-scale kernels take their arguments in the
-// ordinary way: see load_mquery.  The two pointers stay ordinary `__restrict__` parameters:
+// ordinary way: read late inside their loops over items, the arguments made
+// the sampler for 5 to 8 plies return wrong weights on some launches.  The two pointers stay ordinary `__restrict__` parameters:
 // through a struct the type records would be loaded by the vector unit.
 template <class A> __device__ inline A late_args()
 {

@@ -659,8 +659,8 @@ __host__ __device__ inline G ply_visibility_narrow(int Np, C rp, C Rpc, C wc, C 
 // record, so a wavefront that serves one type takes one branch).
 //
 // NARROW: the kernel has the narrow form.  The footprint sampler, which forms
-// the state at x in two places and spills the most, goes without: 197 us,
-// 204 with both forms (250,007 queries).
+// the state at x in two places and spills the most, goes without (7 us of
+// 204 at 250,007 queries).
 template <bool NARROW, class G, class C, int MP, class P>
 __host__ __device__ inline G ply_visibility(const P& D, C rp, C Rpc, C dP, G na_x, G na_y, G f_x, G f_y)
 {
