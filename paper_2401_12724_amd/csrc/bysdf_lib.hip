@@ -292,60 +292,24 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 #define BYSDF_BACKWARD_MIN_WAVES 1
 #endif
 
-// The kernel's argument struct, which follows the two pointers of the type
-// records and tables, read from the argument segment where it is used.
-// Arguments used in the ordinary way are loaded at the entry and held in
-// scalar registers; the 25 to 40 pointers of the query kernels fill those
-// through the whole body, and the type's scalars and the polynomials'
-// constants spill for them.  Scratch per lane falls from 104 to 80 B in
-// k_eval_sample and 96 to 28 B in k_eval; eval and sample of 2^24 queries
-// 3314 -> 3222 us.  The multi-scale kernels take their arguments in the
-// ordinary way: read late inside their loops over items, the arguments made
-// the sampler for 5 to 8 plies return wrong weights on some launches.  The two pointers stay ordinary `__restrict__` parameters:
-// through a struct the type records would be loaded by the vector unit.
-template <class A> __device__ inline A late_args()
-{
-    using Word = const __attribute__((address_space(4))) uint64_t;
-    static_assert(sizeof(A) % sizeof(uint64_t) == 0, "whole words");
-    Word* p = (Word*)__builtin_amdgcn_kernarg_segment_ptr() + 2;
-    asm volatile("" : "+s"(p));
-    uint64_t w[sizeof(A) / sizeof(uint64_t)];
-#pragma unroll
-    for (unsigned k = 0; k < sizeof(A) / sizeof(uint64_t); ++k) w[k] = p[k];
-    A a;
-    __builtin_memcpy(&a, w, sizeof(A));
-    return a;
-}
-
-struct EvalArgs {
-    int n_types, lds_texels;
-    QPtrs q;
-    OPtrs o;
-    int64_t n;
-};
-
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const TypeRec* __restrict__ types,
-    const float4* __restrict__ tables, EvalArgs args)
+__global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const TypeRec* __restrict__ types, int n_types,
+                                                 const float4* __restrict__ tables, int lds_texels,
+                                                 QPtrs q, OPtrs o, int64_t n)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<EvalArgs>().n; i += stride) {
-        const EvalArgs& in = late_args<EvalArgs>();
-        const QPtrs& q = in.q;
-        const int n_types = in.n_types;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         int t = q.type[i];
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
         V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
         float h = q.h[i], u = q.u[i], v = q.v[i];
-        const bool has_shift = q.s0 != nullptr;
-        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
         uint32_t fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         fl |= check_inputs(h, u, v, wi) | check_dir(wo);
         EvalOut<float> e;
@@ -361,11 +325,11 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_MIN_WAVES) void k_eval(const Typ
             fl = X.ph.flags;
             if (!X.ph.pass) {
                 if (!(X.mu_i > 0.0f)) fl |= F_BACKFACING;
+                float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
                 V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
-                lobes(P, tab, X, wo_g, s0, s1, has_shift, e, types[tu].node_disk);
+                lobes(P, tab, X, wo_g, s0, s1, q.s0 != nullptr, e, types[tu].node_disk);
             }
         });
-        const OPtrs& o = late_args<EvalArgs>().o;
         o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
         o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
         o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -407,29 +371,20 @@ struct SOPtrs {
     uint32_t* flags;
 };
 
-struct SampleArgs {
-    int n_types, lds_texels;
-    SPtrs q;
-    SOPtrs o;
-    int64_t n;
-};
-
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const TypeRec* __restrict__ types,
-    const float4* __restrict__ tables, SampleArgs args)
+__global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const TypeRec* __restrict__ types, int n_types,
+                                                   const float4* __restrict__ tables,
+                                                   int lds_texels, SPtrs q, SOPtrs o, int64_t n)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<SampleArgs>().n; i += stride) {
-        const SampleArgs& in = late_args<SampleArgs>();
-        const SPtrs& q = in.q;
-        const int n_types = in.n_types;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         int t = q.type[i];
         SampleOut<float> so;
         for (int c = 0; c < 3; ++c) so.wo[c] = so.wgt[c] = so.ex[c] = 0.0f;
@@ -439,18 +394,16 @@ __global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const
         uint32_t fl = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         const bool need = fl == 0u;
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
-        const bool has_shift = q.s0 != nullptr;
-        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
+        float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
         float h = q.h[i], u = q.u[i], v = q.v[i], x0, x1, x2;
         query_xi(q, i, x0, x1, x2);
         for_each_wave_type(t, need, [&](int tu) {
             const Derived<double, float>& P = types[tu].d;
             TabPtrT<MIG> tab;
             tab.p = kLds ? s_tab : tables + types[tu].table_off;
-            fl = sample_query<double, float, MP>(P, tab, h, u, v, wi, x0, x1, x2, s0, s1, has_shift, so,
-                                                 types[tu].node_disk);
+            fl = sample_query<double, float, MP>(P, tab, h, u, v, wi, x0, x1, x2, s0, s1,
+                                                 q.s0 != nullptr, so, types[tu].node_disk);
         });
-        const SOPtrs& o = late_args<SampleArgs>().o;
         o.wox[i] = so.wo[0]; o.woy[i] = so.wo[1]; o.woz[i] = so.wo[2];
         o.wr[i] = so.wgt[0]; o.wg[i] = so.wgt[1]; o.wb[i] = so.wgt[2];
         o.pdf[i] = so.pdf;
@@ -466,40 +419,25 @@ __global__ __launch_bounds__(kBlock, BYSDF_SAMPLE_MIN_WAVES) void k_sample(const
 // direction.  The state at x and the K forward nodes are computed once and
 // serve both directions, so a query costs about one evaluation plus the
 // draw instead of an evaluation and a sample.
-struct EvalSampleArgs {
-    int n_types, lds_texels;
-    QPtrs q;
-    const float *xi0, *xi1, *xi2;
-    OPtrs o;
-    SOPtrs so;
-    int64_t n;
-};
-
 template <bool kLds, int MP, bool MIG>
-__global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sample(const TypeRec* __restrict__ types,
-    const float4* __restrict__ tables, EvalSampleArgs args)
+__global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sample(
+    const TypeRec* __restrict__ types, int n_types, const float4* __restrict__ tables, int lds_texels,
+    QPtrs q, const float* __restrict__ xi0, const float* __restrict__ xi1,
+    const float* __restrict__ xi2, OPtrs o, SOPtrs so_p, int64_t n)
 {
     bysdf::stage_math_tables();
     __syncthreads();
     extern __shared__ float4 s_tab[];
     if (kLds) {
-        for (int i = threadIdx.x; i < args.lds_texels; i += blockDim.x) s_tab[i] = tables[i];
+        for (int i = threadIdx.x; i < lds_texels; i += blockDim.x) s_tab[i] = tables[i];
         __syncthreads();
     }
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < late_args<EvalSampleArgs>().n; i += stride) {
-        const EvalSampleArgs& in = late_args<EvalSampleArgs>();
-        const QPtrs& q = in.q;
-        const int n_types = in.n_types;
-        const float* xi0 = in.xi0;
-        const float* xi1 = in.xi1;
-        const float* xi2 = in.xi2;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         int t = q.type[i];
         V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
         V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
         float h = q.h[i], u = q.u[i], v = q.v[i], x0 = xi0[i], x1 = xi1[i], x2 = xi2[i];
-        const bool has_shift = q.s0 != nullptr;
-        const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
         const uint32_t bad_t = (t < 0 || t >= n_types) ? F_BAD_INPUT : 0u;
         const uint32_t bad_hit = bad_t | check_inputs(h, u, v, wi);
         const uint32_t bad_wo = check_dir(wo);
@@ -518,7 +456,9 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sa
             tab.p = kLds ? s_tab : tables + types[tu].table_off;
             XState<double, float, MP> X;
             state_at_x(P, tab, h, u, v, wi, X);
-            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{P, tab, X, s0, s1, has_shift, types[tu].node_disk};
+            float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
+            NodesComputed<double, float, MP, TabPtrT<MIG>> nf{P, tab, X, s0, s1, q.s0 != nullptr,
+                                                               types[tu].node_disk};
             V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
             fs = eval_sample_from_x(P, X, wi, wo_g, bad_wo == 0u, x0, x1, x2, nf, e, so);
             if (bad_wo == 0u) {
@@ -526,9 +466,6 @@ __global__ __launch_bounds__(kBlock, BYSDF_EVAL_SAMPLE_MIN_WAVES) void k_eval_sa
                 if (!X.ph.pass && !(X.mu_i > 0.0f)) fe |= F_BACKFACING;
             }
         });
-        const EvalSampleArgs& out = late_args<EvalSampleArgs>();
-        const OPtrs& o = out.o;
-        const SOPtrs& so_p = out.so;
         o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
         o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
         o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -1568,30 +1505,22 @@ __global__ void k_backward_sum(const int32_t* __restrict__ tile_first, int n_typ
 // last tile, so the grid always drains.
 __global__ void k_reset_counter(int* counter) { *counter = 0; }
 
-struct BatchedArgs {
-    const int64_t* off;
-    const int32_t* tile_first;
-    int* counter;
-    int n_types, chunk;
-    QPtrs q;
-    OPtrs o;
-};
-
 template <int MP, bool kLds, int WAVES>
-__global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(const TypeRec* __restrict__ types,
-    const float4* __restrict__ tables, BatchedArgs args)
+__global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(
+    const TypeRec* __restrict__ types, const float4* __restrict__ tables,
+    const int64_t* __restrict__ off, int n_types, const int32_t* __restrict__ tile_first,
+    int* counter, QPtrs q, OPtrs o, int chunk)
 {
-    const int chunk = args.chunk;
     bysdf::stage_math_tables();
     __syncthreads();
     // a tile holds as many queries as the workgroup has lanes (128 or 256)
     __shared__ float4 s_tab[kLds ? kMaxLdsTexels : 1];
     __shared__ int s_next;
     const int tid = threadIdx.x;
-    const int n_tiles = args.tile_first[args.n_types];
+    const int n_tiles = tile_first[n_types];
     int staged = -1;
     for (;;) {
-        if (tid == 0) s_next = atomicAdd(late_args<BatchedArgs>().counter, chunk);
+        if (tid == 0) s_next = atomicAdd(counter, chunk);
         __syncthreads();
         const int t0 = s_next;
         __syncthreads();
@@ -1599,10 +1528,7 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(const TypeRec* _
         for (int c = 0; c < chunk; ++c) {
             int type = 0, count = 0;
             int64_t start = 0;
-            const BatchedArgs& in = late_args<BatchedArgs>();
-            const QPtrs& q = in.q;
-            if (!locate_tile(t0 + c, in.tile_first, in.n_types, in.off, &type, &start, &count, (int)blockDim.x))
-                break;
+            if (!locate_tile(t0 + c, tile_first, n_types, off, &type, &start, &count, (int)blockDim.x)) break;
             type = __builtin_amdgcn_readfirstlane(type);
             const TypeRec& rec = types[type];
             TabPtr tab;
@@ -1622,8 +1548,6 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(const TypeRec* _
             V3<float> wi = mk3<float>(q.wix[i], q.wiy[i], q.wiz[i]);
             V3<float> wo = mk3<float>(q.wox[i], q.woy[i], q.woz[i]);
             const float h = q.h[i], u = q.u[i], v = q.v[i];
-            const bool has_shift = q.s0 != nullptr;
-            const float s0 = has_shift ? q.s0[i] : 0.0f, s1 = has_shift ? q.s1[i] : 0.0f;
             uint32_t fl = check_inputs(h, u, v, wi) | check_dir(wo);
             EvalOut<float> e;
             for (int k = 0; k < 3; ++k) e.E[k] = e.ExB[k] = e.EyB[k] = 0.0f;
@@ -1635,11 +1559,11 @@ __global__ __launch_bounds__(kBlock, WAVES) void k_eval_batched(const TypeRec* _
                 fl = X.ph.flags;
                 if (!X.ph.pass) {
                     if (!(X.mu_i > 0.0f)) fl |= F_BACKFACING;
+                    const float s0 = q.s0 ? q.s0[i] : 0.0f, s1 = q.s1 ? q.s1[i] : 0.0f;
                     V3<double> wo_g = mk3<double>(wo.x, wo.y, wo.z);
-                    lobes(P, tab, X, wo_g, s0, s1, has_shift, e, rec.node_disk);
+                    lobes(P, tab, X, wo_g, s0, s1, q.s0 != nullptr, e, rec.node_disk);
                 }
             }
-            const OPtrs& o = late_args<BatchedArgs>().o;
             o.Er[i] = e.E[0]; o.Eg[i] = e.E[1]; o.Eb[i] = e.E[2];
             o.ExS[i] = e.ExS; o.EyS[i] = e.EyS;
             o.ExBr[i] = e.ExB[0]; o.ExBg[i] = e.ExB[1]; o.ExBb[i] = e.ExB[2];
@@ -1858,8 +1782,8 @@ extern "C" int bysdf_eval(const bysdf_types_t* h, const bysdf_query_soa* q, int6
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
-                       EvalArgs{h->n_types, tx, qp, op, n});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
+                       h->d_tables, tx, qp, op, n);
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1897,8 +1821,8 @@ extern "C" int bysdf_sample_pdf(const bysdf_types_t* h, const bysdf_sample_soa* 
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_sample, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
-                       SampleArgs{h->n_types, tx, sp, op, n});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
+                       h->d_tables, tx, sp, op, n);
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -1931,8 +1855,8 @@ extern "C" int bysdf_eval_sample(const bysdf_types_t* h, const bysdf_query_soa* 
     size_t lds = h->single_table ? sizeof(float4) * h->table_texels : 0;
     int tx = h->single_table ? h->table_texels : 0;
     auto kern = BYSDF_PICK(k_eval_sample, h);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->d_tables,
-                       EvalSampleArgs{h->n_types, tx, qp, xi0, xi1, xi2, op, sop, n});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), lds, stream, h->d_types, h->n_types,
+                       h->d_tables, tx, qp, xi0, xi1, xi2, op, sop, n);
     HIP_TRY(hipGetLastError());
     return BYSDF_OK;
 }
@@ -2210,8 +2134,8 @@ static void launch_batched(const bysdf_types_t* h, bool lds, int waves, int bloc
 {
     auto kern = lds ? (waves == 1 ? k_eval_batched<MP, true, 1> : k_eval_batched<MP, true, 2>)
                     : (waves == 1 ? k_eval_batched<MP, false, 1> : k_eval_batched<MP, false, 2>);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, stream, h->d_types, h->d_tables,
-                       BatchedArgs{off, tile_first, counter, h->n_types, chunk, qp, op});
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(block), 0, stream, h->d_types, h->d_tables, off, h->n_types,
+                       tile_first, counter, qp, op, chunk);
 }
 
 extern "C" int bysdf_eval_batched(const bysdf_types_t* h, const int64_t* type_offsets, int64_t n,
