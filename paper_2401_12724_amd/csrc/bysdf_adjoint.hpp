@@ -642,9 +642,10 @@ __host__ __device__ inline void at_x_adjoint(const Derived<double, float>& P, co
     }
     const float mp = front ? mu_i : 0.0f;
     const float im = rcp_(mp + mu_o), fls = float(1.0 / (4.0 * kPi)) * im, sh = fls + float(1.0 / kPi);
-    body = X.body * sh * mu_o;
-    const float fls_ = -w_body * X.body * mu_o * fls * im;  // through mp + mu_o
-    mu_o_ = w_body * X.body * sh + fls_;
+    const float bf = P.B * P.r * X.ils;
+    body = bf * sh * mu_o;
+    const float fls_ = -w_body * bf * mu_o * fls * im;  // through mp + mu_o
+    mu_o_ = w_body * bf * sh + fls_;
     if (front) {
         // body factor B r / (1 + a(mu_i))
         mu_i_ += fls_ - w_body * body * rcp_(1.0f + ls_albedo(mu_i)) * ls_albedo_dmu(mu_i);

@@ -113,7 +113,7 @@ __host__ __device__ inline void fill_derived(TypeRec& t)
     d.ax = (float)t.beta;
     d.ay = (float)(t.beta * t.aniso);
     d.eta = (float)t.eta;
-    d.inv_eta2 = (float)(1.0 / (t.eta * t.eta));
+    d.inv_eta2 = (float)(1.0 / (double)(d.eta * d.eta));
     d.kS = t.k_spec; d.B = t.B; d.r = t.r; d.sigma_t = t.sigma_t;
     d.rho_p = t.ply_density; d.rho_f = t.fiber_density; d.dP = t.shadow_hw;
     for (int c = 0; c < 3; ++c) d.alb[c] = t.albedo[c];
@@ -187,7 +187,11 @@ template <class S> __host__ __device__ inline S fresnel(S c, S e)
 
 // Fresnel transmittance 1 - F written without the cancellation of 1 - F
 // near total internal reflection: 1 - r^2 = 4 c e c_t / (c + e c_t)^2 per
-// polarisation, the two quotients over one denominator.  ie2 = 1 / e^2.
+// polarisation.  ie2 = 1 / e^2.  In single precision the quotients stay apart:
+// over one denominator they round three times more, which took E_yS 3 % further
+// from 64 bits (relative 2-norm over 2^24 hits 15.7e-8 to 16.2e-8) and saved
+// nothing.  In double that is far below the result's precision and saves a
+// reciprocal.
 template <class S> __host__ __device__ inline S fresnel_T(S c, S e, S ie2)
 {
     S s2t = (S(1) - c * c) * ie2;
@@ -195,6 +199,7 @@ template <class S> __host__ __device__ inline S fresnel_T(S c, S e, S ie2)
     S ct = sqrt_(S(1) - s2t);
     S a = c + e * ct, b = e * c + ct;
     S a2 = a * a, b2 = b * b;
+    if (sizeof(S) == sizeof(float)) return S(2) * e * c * ct * (rcp_(a2) + rcp_(b2));
     return S(2) * e * c * ct * (a2 + b2) * rcp_(a2 * b2);
 }
 
@@ -681,8 +686,8 @@ template <class G, class S, int MP> struct XState {
     S Gp, Gf, mu_i;
     S w[4];           // lobe selection weights
     // terms of the lobes at x that do not depend on wo: Smith's G1 towards wi
-    // (isotropic), 1 / (4 mu_i), and the reflected body lobe's factor
-    S g1i, q4, body;
+    // (isotropic), 1 / (4 mu_i), and 1 / (1 + a(mu_i)) of the body lobe
+    S g1i, q4, ils;
     G ca, sa;         // angle around the hit ply
     G rawp, rawf;     // visibilities before the density blends
 };
@@ -701,7 +706,7 @@ __host__ __device__ inline void lobe_weights(const Derived<G, S>& P, XState<G, S
     const G iz = dot(X.wi_g, X.fx.n);
     X.g1i = front ? smith_G1_front<S>(X.mu_i, Narrow<S>::from(one_minus_sq(iz)), P.ax) : S(0);
     X.q4 = front ? rcp_(S(4) * X.mu_i) : S(0);
-    X.body = P.B * P.r * rcp_(S(1) + ls_albedo<S>(front ? X.mu_i : S(0)));
+    X.ils = rcp_(S(1) + ls_albedo<S>(front ? X.mu_i : S(0)));
 }
 
 template <bool NARROW, class G, class S, int MP, class Tab>
@@ -1022,7 +1027,7 @@ __host__ __device__ inline void lobes_at_x(const Derived<G, S>& P, const XState<
     if (val(mu_o_g) > 0.0) {
         S mp = front_i ? mu_i : S(0);
         S fls = rcp_(S(float(4.0 * kPi)) * (mp + mu_o));
-        bxu = X.body * (fls + S(float(1.0 / kPi))) * mu_o;
+        bxu = P.B * P.r * (fls + S(float(1.0 / kPi))) * mu_o * X.ils;
         pxB = mu_o * S(float(1.0 / kPi));
     }
     a.ExS = ExS;

@@ -125,3 +125,13 @@ extern "C" int bysdf_audit_sample(const bysdf_type_params* p, const float* table
     }
     return 0;
 }
+
+// The lobes' Fresnel transmittance of cosines c (n) into the index eta, in
+// single precision as the forward nodes form it.
+extern "C" int bysdf_audit_transmittance(int64_t n, const float* c, float eta, float* out)
+{
+    if (n < 0 || !c || !out) return -1;
+    const float ie2 = (float)(1.0 / (double)(eta * eta));
+    for (int64_t i = 0; i < n; ++i) out[i] = fresnel_T<float>(c[i], eta, ie2);
+    return 0;
+}

@@ -1,6 +1,8 @@
 """How the model's formulas round, measured on the host: libbysdf_audit runs
 the kernels' templates with chosen stages in single precision, so an
 ill-conditioned form shows as an error far above its neighbours'."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -36,3 +38,27 @@ def test_exit_refraction_conditioning():
     first = _exit_error(1.2)
     for eta in (1.249, 1.251, 1.3, 1.4):
         assert _exit_error(eta) <= 1.1 * first, eta
+
+
+@pytest.mark.parametrize("eta", [1.1, 1.3, 1.55, 2.4])
+def test_transmittance_rounding(eta):
+    """The nodes' transmittance rounds no more than its textbook form, one
+    quotient per polarisation (4 c e c_t / (c + e c_t)^2 and the like), does
+    in single precision; 2 % covers the sampling of the rms over 10^6 cosines
+    (0.1 %) and fused products."""
+    n = 1 << 20
+    c = np.random.default_rng(2).uniform(0.02, 1.0, n).astype(np.float32)
+    got = np.zeros(n, np.float32)
+    lib = A.lib()
+    lib.bysdf_audit_transmittance.argtypes = [C.c_int64, C.c_void_p, C.c_float, C.c_void_p]
+    assert lib.bysdf_audit_transmittance(n, A._ptr(c), eta, A._ptr(got)) == 0
+
+    def form(c, e):
+        one, two = c.dtype.type(1), c.dtype.type(2)
+        ct = np.sqrt(one - (one - c * c) * (one / (e * e)))
+        a, b = c + e * ct, e * c + ct
+        return two * e * c * ct * (one / (a * a) + one / (b * b))
+
+    exact = form(c.astype(np.float64), np.float64(np.float32(eta)))
+    rms = lambda x: np.sqrt(np.mean(((x - exact) / exact) ** 2))
+    assert rms(got) <= 1.02 * rms(form(c, np.float32(eta)))
