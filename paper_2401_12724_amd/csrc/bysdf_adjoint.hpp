@@ -683,7 +683,7 @@ __host__ __device__ inline bool adjoint_query(const TypeRec& rec, const Tab& tab
     {
         const double fx = X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y, fy = X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x;
         const double da = ht.omega - dth;
-        raw = ply_visibility<true, Dual, double, MP>(P, P.rp, P.Rpc, (double)P.dP, Dual(X.ca, -X.sa * da),
+        raw = ply_visibility<Dual, double, MP>(P, P.rp, P.Rpc, (double)P.dP, Dual(X.ca, -X.sa * da),
                                                Dual(X.sa, X.ca * da), Dual(fx, fy * ht.omega),
                                                Dual(fy, -fx * ht.omega));
     }

@@ -662,14 +662,10 @@ __host__ __device__ inline G ply_visibility_narrow(int Np, C rp, C Rpc, C wc, C 
 // incident direction in the ply hit's frame, (cosine, sine) of phi times any
 // length: the narrow form for the types that allow it (settled by the
 // record, so a wavefront that serves one type takes one branch).
-//
-// NARROW: the kernel has the narrow form.  The footprint sampler, which forms
-// the state at x in two places and spills the most, goes without (7 us of
-// 204 at 250,007 queries).
-template <bool NARROW, class G, class C, int MP, class P>
+template <class G, class C, int MP, class P>
 __host__ __device__ inline G ply_visibility(const P& D, C rp, C Rpc, C dP, G na_x, G na_y, G f_x, G f_y)
 {
-    if (NARROW && D.win_narrow)
+    if (D.win_narrow)
         return ply_visibility_narrow<G, C, MP>(D.Np, rp, Rpc, C(D.win_c), C(D.win_s), C(D.win_i), na_x, na_y, f_x, f_y,
                                                D.ply_c, D.ply_s);
     return ply_shadow_raw<G, MP>(D.Np, G(rp), G(Rpc), G(dP), na_x, na_y, atan2_(f_y, f_x), D.ply_c, D.ply_s);
@@ -709,7 +705,7 @@ __host__ __device__ inline void lobe_weights(const Derived<G, S>& P, XState<G, S
     X.ils = rcp_(S(1) + ls_albedo<S>(front ? X.mu_i : S(0)));
 }
 
-template <bool NARROW, class G, class S, int MP, class Tab>
+template <class G, class S, int MP, class Tab>
 __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const Tab& tab, const V3<float>& wi,
                                                   XState<G, S, MP>& X)
 {
@@ -728,7 +724,7 @@ __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const 
     G raw;
     {
         StageMark<G> mark(kStageShadow);
-        raw = ply_visibility<NARROW, G, G, MP>(P, P.rp, P.Rpc, G(val(P.dP)), X.ca, X.sa,
+        raw = ply_visibility<G, G, MP>(P, P.rp, P.Rpc, G(val(P.dP)), X.ca, X.sa,
                                        X.ph.n2x * X.wi_g.x + X.ph.n2y * X.wi_g.y,
                                        X.ph.n2x * X.wi_g.y - X.ph.n2y * X.wi_g.x);
     }
@@ -736,23 +732,24 @@ __host__ __device__ inline void state_after_plies(const Derived<G, S>& P, const 
     X.rawf = gft;
     X.Gp = Narrow<S>::from(G(1) - G(val(P.rho_p)) * (G(1) - raw));
     X.Gf = Narrow<S>::from(G(1) - G(val(P.rho_f)) * (G(1) - gft));
-    lobe_weights(P, X);
 }
 
-// Everything at x that does not depend on wo: ply hit, fiber frame,
-// shadowing, lobe weights.
-template <bool NARROW, class G, class S, int MP, class Tab>
-__host__ __device__ inline void state_at_x_of(const Derived<G, S>& P, const Tab& tab, float h, float u,
-                                              float v, const V3<float>& wi, XState<G, S, MP>& X)
+// What a hit fixes: ply hit, fiber frame, shadowing.
+template <class G, class S, int MP, class Tab>
+__host__ __device__ inline void hit_state(const Derived<G, S>& P, const Tab& tab, float h, float u, float v,
+                                          const V3<float>& wi, XState<G, S, MP>& X)
 {
     trace_plies(P, h, u, v, wi, X.ph);
-    state_after_plies<NARROW>(P, tab, wi, X);
+    state_after_plies(P, tab, wi, X);
 }
+// Everything at x that does not depend on wo: the hit's state and the lobe
+// weights.
 template <class G, class S, int MP, class Tab>
 __host__ __device__ inline void state_at_x(const Derived<G, S>& P, const Tab& tab, float h, float u,
                                            float v, const V3<float>& wi, XState<G, S, MP>& X)
 {
-    state_at_x_of<true>(P, tab, h, u, v, wi, X);
+    hit_state(P, tab, h, u, v, wi, X);
+    if (!X.ph.pass) lobe_weights(P, X);
 }
 
 // ---------------------------------------------------------------- forward nodes

