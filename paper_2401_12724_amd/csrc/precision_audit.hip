@@ -13,6 +13,7 @@
 // device's sequences).  Returns 0, or -1 on a bad argument.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdint>
 #include <vector>
 
@@ -20,6 +21,7 @@
 #include "bysdf_model.hpp"
 #include "bysdf_precision.hpp"
 #include "lib_internal.hpp"
+#include "yarn_tube.hpp"
 
 namespace bysdf {
 thread_local unsigned g_audit_mask = 0u;
@@ -133,5 +135,32 @@ extern "C" int bysdf_audit_transmittance(int64_t n, const float* c, float eta, f
     if (n < 0 || !c || !out) return -1;
     const float ie2 = (float)(1.0 / (double)(eta * eta));
     for (int64_t i = 0; i < n; ++i) out[i] = fresnel_T<float>(c[i], eta, ie2);
+    return 0;
+}
+
+// n rays against a span each (rays 3 x n, control points 4 x n x (x, y, z, R)):
+// the best of nsamp + 1 samples as the traversal's scan ranks them (sampled,
+// +inf for none) and the entry at that sample that the hit is decided by.
+extern "C" int bysdf_audit_span(int64_t n, const float* ctrl, const float* o, const float* d, int nsamp,
+                                double* sampled, double* entry)
+{
+    if (n < 0 || nsamp < 1 || !ctrl || !o || !d || !sampled || !entry) return -1;
+    for (int64_t i = 0; i < n; ++i) {
+        yarn::SpanGeo g;
+        for (int k = 0; k < 4; ++k) {
+            const float* c = ctrl + 4 * (k * n + i);
+            g.c[k] = yarn::d3((double)c[0] - o[i], (double)c[1] - o[n + i], (double)c[2] - o[2 * n + i]);
+            if (k == 0) g.R = (double)c[3];
+        }
+        const yarn::D3 dir = yarn::unit(yarn::d3(d[i], d[n + i], d[2 * n + i]));
+        yarn::D3 e1, e2;
+        yarn::across_ray(dir, &e1, &e2);
+        yarn::SpanView v;
+        int at = -1;
+        sampled[i] = entry[i] = INFINITY;
+        if (!yarn::span_view(g, dir, e1, e2, 0.0, 1e30, nsamp, &v)) continue;
+        yarn::span_sample(v, 0.0, 0, 1, nsamp, &sampled[i], &at);
+        if (at >= 0) entry[i] = yarn::sample_entry(g, dir, e1, e2, nsamp, at);
+    }
     return 0;
 }

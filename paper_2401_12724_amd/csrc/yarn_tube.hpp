@@ -186,6 +186,14 @@ __host__ __device__ inline bool entry_slope(const RayCubic& rc, double R, double
     return true;
 }
 
+// Two unit vectors across a ray of direction d.
+__host__ __device__ inline void across_ray(D3 d, D3* e1, D3* e2)
+{
+    const D3 a = fabs(d.x) < 0.9 ? d3(1, 0, 0) : d3(0, 1, 0);
+    *e1 = unit(cross(d, a));
+    *e2 = cross(d, *e1);
+}
+
 // A span to sample: its view from the ray, R^2 and 1 / samples.
 struct SpanView {
     RayCubic rc;
@@ -194,8 +202,8 @@ struct SpanView {
 
 // Whether a span may be entered at t_min < t <= t_lim: false when the hull of
 // its control points misses the ray's R-slab in that range.  Fills its view.
-__device__ inline bool span_view(const SpanGeo& g, D3 d, D3 e1, D3 e2, double t_min, double t_lim, int nsamp,
-                                 SpanView* v)
+__host__ __device__ inline bool span_view(const SpanGeo& g, D3 d, D3 e1, D3 e2, double t_min, double t_lim,
+                                          int nsamp, SpanView* v)
 {
     const double R = g.R;
     bool all_pu = true, all_nu = true, all_pw = true, all_nw = true, all_b = true, all_f = true;
@@ -244,8 +252,8 @@ __device__ inline bool span_view(const SpanGeo& g, D3 d, D3 e1, D3 e2, double t_
 
 // The smallest entry T(s_i) > t_min over the samples i = i0, i0 + di, ... <=
 // nsamp and its index (+inf, -1: none).
-__device__ inline void span_sample(const SpanView& v, double t_min, int i0, int di, int nsamp, double* t_out,
-                                   int* i_out)
+__host__ __device__ inline void span_sample(const SpanView& v, double t_min, int i0, int di, int nsamp,
+                                            double* t_out, int* i_out)
 {
     double bt = INFINITY;
     int bi = -1;
@@ -268,8 +276,15 @@ __device__ inline void span_sample(const SpanView& v, double t_min, int i0, int 
 // The entry at sample bi of a span whose ball there meets the ray.  Where two
 // spans join, both hold the same entry up to rounding, and the last bits of
 // this value and of the refined one say which of them is reported; every
-// product is fused as written, so that all kernels report the same span.
-__device__ inline double sample_entry(const SpanGeo& g, D3 d, D3 e1, D3 e2, int nsamp, int bi)
+// product is fused as written, so that all kernels report the same span.  The
+// order of the z projection's products differs between even and odd control
+// points for no reason of geometry: it is the order in which the compiler
+// fused them when the traversal had one lane per ray, kept so that the span
+// reported at a joint stays the same.
+// The scan decided that the ball meets the ray from products fused in another
+// order; a ray that touches the ball may have a half chord squared below zero
+// here, by rounding, and it is zero then.
+__host__ __device__ inline double sample_entry(const SpanGeo& g, D3 d, D3 e1, D3 e2, int nsamp, int bi)
 {
 #pragma clang fp contract(off)
     auto across = [](D3 a, D3 b) { return fma(a.z, b.z, fma(a.x, b.x, a.y * b.y)); };
@@ -288,7 +303,7 @@ __device__ inline double sample_entry(const SpanGeo& g, D3 d, D3 e1, D3 e2, int 
     }
     const double s = bi * (1.0 / nsamp), u = power(pu, s), w = power(pw, s);
     const double q2 = g.R * g.R - fma(u, u, w * w);
-    return power(pz, s) - bysdf::sqrt_(q2);
+    return power(pz, s) - bysdf::sqrt_(fmax(q2, 0.0));
 }
 
 // Minimum of T in the bracket of sample bi (best sampled value bt):
@@ -709,8 +724,8 @@ struct WaveRays {
         dx[l] = d.x;
         dy[l] = d.y;
         dz[l] = d.z;
-        const D3 a = fabs(d.x) < 0.9 ? d3(1, 0, 0) : d3(0, 1, 0);
-        const D3 e1 = unit(cross(d, a)), e2 = cross(d, e1);
+        D3 e1, e2;
+        across_ray(d, &e1, &e2);
         e1x[l] = e1.x;
         e1y[l] = e1.y;
         e1z[l] = e1.z;
