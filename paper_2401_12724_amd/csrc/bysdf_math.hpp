@@ -101,15 +101,28 @@ __host__ __device__ inline double sqrt_(double x)
     return sqrt(x);
 #endif
 }
-// Estimate of 1 / sqrt(x) to about 1e-7 (the device's instruction); NaN for
-// x < 0, infinite for 0.
+// Estimate of 1 / sqrt(x) to about 1e-7 (the device's instruction; on the
+// host the value rounded to 24 bits); NaN for x < 0, infinite for 0.
 __host__ __device__ inline double rsq_estimate(double x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __builtin_amdgcn_rsq(x);
 #else
-    return 1.0 / sqrt(x);
+    int e;
+    const double m = frexp(1.0 / sqrt(x), &e);
+    return ldexp((double)(float)m, e);
 #endif
+}
+// sqrt_ for an argument that is used only where it is positive: within an ulp
+// of the rounded root there, NaN elsewhere (also at 0).  The refinement of
+// half the reciprocal and the case of 0 are left out: the last correction is
+// of relative size 1e-14, so an estimate's 1e-7 in its factor does not show.
+__host__ __device__ inline double sqrt_positive(double x)
+{
+    const double y = rsq_estimate(x), hy = 0.5 * y;
+    double g = x * y;
+    g = fma(g, fma(-hy, g, 0.5), g);
+    return fma(fma(-g, g, x), hy, g);
 }
 // reciprocal square root (the device uses the hardware estimate refined by
 // the math library; the host path only serves host-side tools)

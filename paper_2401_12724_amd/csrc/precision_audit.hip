@@ -164,3 +164,11 @@ extern "C" int bysdf_audit_span(int64_t n, const float* ctrl, const float* o, co
     }
     return 0;
 }
+
+// The root the scan takes of a sample's half chord squared, of n positive x.
+extern "C" int bysdf_audit_sqrt(int64_t n, const double* x, double* out)
+{
+    if (n < 0 || !x || !out) return -1;
+    for (int64_t i = 0; i < n; ++i) out[i] = sqrt_positive(x[i]);
+    return 0;
+}

@@ -260,11 +260,9 @@ __host__ __device__ inline void span_sample(const SpanView& v, double t_min, int
     for (int i = i0; i <= nsamp; i += di) {
         const double s = i * v.inv, u = horner3(v.rc.u, s), w = horner3(v.rc.w, s);
         const double q2 = fma(-u, u, fma(-w, w, v.R2));
-        // the root from the hardware estimate and one correction, within a
-        // few ulps; a ball that misses the ray (q2 <= 0) makes it a NaN, which
-        // no comparison takes
-        const double y = bysdf::rsq_estimate(q2), q = q2 * y;
-        const double t = horner3(v.rc.z, s) - fma(q, fma(-q, 0.5 * y, 0.5), q);
+        // a ball that misses the ray (q2 <= 0) makes the root a NaN, which no
+        // comparison takes
+        const double t = horner3(v.rc.z, s) - bysdf::sqrt_positive(q2);
         const bool in = t > t_min && t < bt;
         bt = in ? t : bt;
         bi = in ? i : bi;

@@ -47,3 +47,19 @@ def test_tangent_rays():
     assert met.sum() > 1000
     assert not np.isnan(entry).any()
     assert np.all(np.abs(entry[met] - sampled[met]) <= 1e-7 * (norm * scale)[met])
+
+
+def test_sample_root():
+    """The root in a sample's entry, refined from an estimate of 24 bits, is
+    within an ulp of the rounded root over the half chords squared of tubes
+    from 1e-6 to 1e3 in radius, down to touching rays."""
+    x = 10.0 ** np.random.default_rng(4).uniform(-28.0, 6.0, 200000)
+    got = np.zeros_like(x)
+    f = A.lib().bysdf_audit_sqrt
+    f.argtypes = [C.c_int64, C.c_void_p, C.c_void_p]
+    assert f(len(x), A._ptr(x), A._ptr(got)) == 0
+    ref = np.sqrt(x)
+    assert np.all(np.abs(got - ref) <= np.spacing(ref))
+    x[0], x[1] = 0.0, -1.0
+    assert f(2, A._ptr(x), A._ptr(got)) == 0
+    assert np.isnan(got[:2]).all()
