@@ -47,6 +47,7 @@ struct HostScene {
     std::vector<SpanRec> span;
     std::vector<float4> frame;
     std::vector<WNode> node;  // the 4-wide tree
+    std::vector<int> up;      // per node, then per span: where it hangs, 4 node + slot (the root: -1)
     std::vector<float> phase;
     std::vector<int> type;
     int depth = 0;
@@ -538,16 +539,22 @@ inline int yarn_scene_build_host(const float* ctrl, const int64_t* off, int32_t 
     if (W.max_depth > kWideDepthMax)
         return build_fail(err, BYSDF_ERR_INVALID_PARAM, "4-wide BVH depth %d exceeds %d", W.max_depth,
                           kWideDepthMax);
+    hs->up.assign(rec_o.size() + W.wide.size(), -1);
     for (WNode& w : W.wide)
         for (WChild& c : w.child) {
             int code, yarn = -1;
+            const int at = 4 * (int)(&w - W.wide.data()) + (int)(&c - w.child);
             memcpy(&code, &c.lo_code.w, sizeof code);
             if (code < 0) {
                 int first, count;
                 decode_leaf(code, &first, &count);
                 yarn = rec_o[first].yarn;
-                for (int k = 1; k < count; ++k)
+                for (int k = 0; k < count; ++k) {
                     if (rec_o[first + k].yarn != yarn) yarn = -1;
+                    hs->up[W.wide.size() + first + k] = at;
+                }
+            } else if (code > 0) {
+                hs->up[code] = at;
             }
             memcpy(&c.hi_yarn.w, &yarn, sizeof yarn);
         }

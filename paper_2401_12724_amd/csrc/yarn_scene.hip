@@ -60,6 +60,7 @@ struct yarn_scene {
     SpanRec* d_span = nullptr;
     float4* d_frame = nullptr;
     WNode* d_node = nullptr;
+    int* d_up = nullptr;
     float* d_phase = nullptr;
     int* d_type = nullptr;
     size_t bytes = 0;
@@ -70,6 +71,7 @@ struct yarn_scene {
         v.span = d_span;
         v.frame = d_frame;
         v.node = d_node;
+        v.up = d_up;
         v.yarn_phase = d_phase;
         v.yarn_type = d_type;
         v.n_nodes = (int)n_nodes;
@@ -117,6 +119,7 @@ static void free_scene(yarn_scene* s)
     (void)hipFree(s->d_span);
     (void)hipFree(s->d_frame);
     (void)hipFree(s->d_node);
+    (void)hipFree(s->d_up);
     (void)hipFree(s->d_phase);
     (void)hipFree(s->d_type);
     delete s;
@@ -177,6 +180,7 @@ extern "C" int yarn_scene_create(const float* ctrl, const int64_t* off, int32_t 
         (rc = up((void**)&s->d_span, rec_o.data(), sizeof(SpanRec) * n_spans)) ||
         (rc = up((void**)&s->d_frame, frame_o.data(), sizeof(float4) * n_spans)) ||
         (rc = up((void**)&s->d_node, B.nodes.data(), sizeof(WNode) * B.nodes.size())) ||
+        (rc = up((void**)&s->d_up, hs.up.data(), sizeof(int) * hs.up.size())) ||
         (rc = up((void**)&s->d_phase, phase.data(), sizeof(float) * n_yarns)) ||
         (rc = up((void**)&s->d_type, type.data(), sizeof(int) * n_yarns))) {
         (void)hipStreamSynchronize(stream);

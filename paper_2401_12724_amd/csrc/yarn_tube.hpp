@@ -79,6 +79,9 @@ struct SceneView {
     const SpanRec* span;    // leaf order
     const float4* frame;    // per span (leaf order): RMF normal at s = 0, arc length at s = 0
     const WNode* node;
+    // per node, then per span: where it or its leaf hangs, 4 node + slot (a
+    // node's index is above its parent's)
+    const int* up;
     const float* yarn_phase;
     const int* yarn_type;
     int n_nodes;
@@ -674,9 +677,8 @@ constexpr double kCandMargin = 0.1;
 struct Candidate {
     double t;  // best sampled entry
     int span;
-    unsigned tag;  // index of the sample (16 bits), lane of the ray (6), number in the search (10, saturated)
+    unsigned tag;  // index of the sample (16 bits), lane of the ray
 };
-constexpr unsigned kLastNumber = 0x3ff;
 // a double's bits in an order-preserving unsigned form, and back
 __device__ inline unsigned long long ordered_bits(double x)
 {
@@ -701,7 +703,7 @@ struct WaveRays {
     unsigned long long key[kRays], key2[kRays];  // the closest entry and its sample, likewise
     double s[kRays];
     float ox[kRays], oy[kRays], oz[kRays];
-    unsigned long long pick[kRays];  // its number in the search << 32 | span
+    int pick[kRays];                             // its span
     int skip[kRays], list[kRays];
     int excl[kMaxExcluded + 1][kRays], n_excl[kRays];  // the ray's Excluded
     int give[kWaveRays];
@@ -731,6 +733,18 @@ struct WaveRays {
         e2y[l] = e2.y;
         e2z[l] = e2.z;
     }
+    // what the box tests of lane l's ray take: its origin, the reciprocal
+    // direction, and the slack of the slab interval, a relative ulp of the
+    // origin along the ray
+    __device__ void box_test(int l, float3& of, float3& inv, float& slack) const
+    {
+        const D3 d = dir(l);
+        of = make_float3(ox[l], oy[l], oz[l]);
+        inv = make_float3(1.0f / (fabs(d.x) > 1e-30 ? (float)d.x : 1e-30f),
+                          1.0f / (fabs(d.y) > 1e-30 ? (float)d.y : 1e-30f),
+                          1.0f / (fabs(d.z) > 1e-30 ? (float)d.z : 1e-30f));
+        slack = 2.4e-7f * (fabsf(of.x) + fabsf(of.y) + fabsf(of.z)) + 1e-30f;
+    }
     // the same ray from another point
     __device__ void move(int l, D3 o, double tmax, int skip_yarn)
     {
@@ -743,9 +757,36 @@ struct WaveRays {
     }
 };
 
+// Whether a ray that searches its tree alone, near children first, meets span
+// a before span b.  Where two spans join, or two yarns coincide, both may hold
+// the same entry to the last bit; this order then says which is reported,
+// whoever scanned them and when.  Only such ties come here.
+__device__ inline bool met_before(const SceneView& S, const WaveRays& W, int ray, int a, int b, double t_min)
+{
+    int ua = S.up[S.n_nodes + a], ub = S.up[S.n_nodes + b];
+    if (ua == ub) return a < b;
+    // up to the node where their ways part
+    while (ua >> 2 != ub >> 2) {
+        if (ua > ub)
+            ua = S.up[ua >> 2];
+        else
+            ub = S.up[ub >> 2];
+    }
+    float3 of, inv;
+    float slack, ta, tb;
+    W.box_test(ray, of, inv, slack);
+    const WChild ca = S.node[ua >> 2].child[ua & 3], cb = S.node[ub >> 2].child[ub & 3];
+    const float t0 = (float)t_min - slack;
+    box_ray(make_float3(ca.lo_code.x, ca.lo_code.y, ca.lo_code.z),
+            make_float3(ca.hi_yarn.x, ca.hi_yarn.y, ca.hi_yarn.z), of, inv, t0, INFINITY, &ta);
+    box_ray(make_float3(cb.lo_code.x, cb.lo_code.y, cb.lo_code.z),
+            make_float3(cb.hi_yarn.x, cb.hi_yarn.y, cb.hi_yarn.z), of, inv, t0, INFINITY, &tb);
+    return ta < tb || (ta == tb && ua < ub);
+}
+
 // Refines the listed candidates [first, first + n), n <= 64, one per lane, and
-// folds them into their rays' closest entries (equal entries, where two spans
-// join: the smaller sample, then the span met first).  A candidate beyond its ray's margin by now is
+// folds them into their rays' closest entries (equal entries: the smaller
+// sample, then met_before).  A candidate beyond its ray's margin by now is
 // dropped.  Called by the whole wavefront.
 __device__ inline void refine_listed(const SceneView& S, WaveRays& W, int first, int n, double t_min)
 {
@@ -753,11 +794,12 @@ __device__ inline void refine_listed(const SceneView& S, WaveRays& W, int first,
     bool ok = lane < n;
     int ray = 0;
     double s = 0.0;
-    unsigned long long key = ~0ull, key2 = ~0ull, pick = ~0ull;
+    unsigned long long key = ~0ull, key2 = ~0ull;
+    int pick = -1;
     if (ok) {
         const Candidate c = W.cand[first + lane];
-        ray = (c.tag >> 16) & 63;
-        pick = (unsigned long long)(c.tag >> 22) << 32 | (unsigned)c.span;
+        ray = c.tag >> 16;
+        pick = c.span;
         const SpanRec r = S.span[c.span];
         const int nsamp = r.info & 0xffff, at = c.tag & 0xffff;
         double bt = 0.0;
@@ -786,7 +828,7 @@ __device__ inline void refine_listed(const SceneView& S, WaveRays& W, int first,
     bool win = ok && W.key[ray] == key;
     if (win && key < before) {
         W.key2[ray] = ~0ull;
-        W.pick[ray] = ~0ull;
+        W.pick[ray] = -1;
     }
     wave_lds_order();
     const unsigned long long before2 = win ? W.key2[ray] : 0ull;
@@ -794,10 +836,20 @@ __device__ inline void refine_listed(const SceneView& S, WaveRays& W, int first,
     if (win) atomicMin(&W.key2[ray], key2);
     wave_lds_order();
     win = win && W.key2[ray] == key2;
-    if (win && key2 < before2) W.pick[ray] = ~0ull;
+    if (win && key2 < before2) W.pick[ray] = -1;
     wave_lds_order();
-    if (win) atomicMin(&W.pick[ray], pick);
+    if (win && W.pick[ray] < 0) W.pick[ray] = pick;
     wave_lds_order();
+    // ties: every round puts an earlier span in the place of each ray that has
+    // one, of at most 64
+    bool tie = win && W.pick[ray] != pick;
+    for (int round = 0; round < 64 && __any((int)tie); ++round) {
+        tie = tie && met_before(S, W, ray, pick, W.pick[ray], t_min);
+        wave_lds_order();
+        if (tie) W.pick[ray] = pick;
+        wave_lds_order();
+        tie = tie && W.pick[ray] != pick;
+    }
     if (win && W.pick[ray] == pick) W.s[ray] = s;
     wave_lds_order();
 }
@@ -838,11 +890,11 @@ __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, b
     const int n = __popcll(m), slot = __popcll(m & ((1ull << lane) - 1ull));
     if (live) {
         W.list[slot] = lane;
-        W.key[lane] = W.key2[lane] = W.pick[lane] = ~0ull;
+        W.key[lane] = W.key2[lane] = ~0ull;
+        W.pick[lane] = -1;
     }
     wave_lds_order();
     int listed = 0, next = 0;
-    unsigned number = 0;  // candidates met so far
     int ray = 0, sp = 0, bottom = 0, code = kTraceDone;
     int leaf = 0;  // the held leaf's code, 0 for none
     float3 of = make_float3(0.f, 0.f, 0.f), inv = of;
@@ -895,13 +947,7 @@ __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, b
             }
         }
         if (take) {
-            const D3 d = W.dir(ray);
-            of = make_float3(W.ox[ray], W.oy[ray], W.oz[ray]);
-            inv = make_float3(1.0f / (fabs(d.x) > 1e-30 ? (float)d.x : 1e-30f),
-                              1.0f / (fabs(d.y) > 1e-30 ? (float)d.y : 1e-30f),
-                              1.0f / (fabs(d.z) > 1e-30 ? (float)d.z : 1e-30f));
-            // widen the slab interval by a relative ulp of the origin along the ray
-            slack = 2.4e-7f * (fabsf(of.x) + fabsf(of.y) + fabsf(of.z)) + 1e-30f;
+            W.box_test(ray, of, inv, slack);
             leaving = W.skip[ray];
             n_excl = W.n_excl[ray];
             sp = bottom = 0;
@@ -1016,23 +1062,21 @@ __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, b
         if (ma) {
             if (add) {
                 const int k = __popcll(ma & ((1ull << lane) - 1ull));
-                W.cand[listed + k] = Candidate{t, span, (unsigned)bi | (unsigned)ray << 16 |
-                                                            min(number + k, kLastNumber) << 22};
+                W.cand[listed + k] = Candidate{t, span, (unsigned)bi | (unsigned)ray << 16};
                 atomicMin(&W.tb[ray], ordered_bits(t));
             }
             wave_lds_order();
             listed += __popcll(ma);
-            number += __popcll(ma);
         }
     }
     RayHit h{INFINITY, 0.0, -1};
     n_ex = 0;
     if (live) {
         n_ex = W.n_excl[lane] - (W.skip[lane] >= 0 ? 1 : 0);
-        if (W.pick[lane] != ~0ull) {
+        if (W.pick[lane] >= 0) {
             h.t = from_ordered(W.key[lane]);
             h.s = W.s[lane];
-            h.span = (int)W.pick[lane];
+            h.span = W.pick[lane];
         }
     }
     wave_lds_order();
