@@ -1641,6 +1641,10 @@ static int types_create(const bysdf_type_params* p, int32_t n_types, bysdf_types
         uint32_t seed;
     };
     std::vector<Job> jobs;
+    // the first type of each node count: the disc points are formed once for all
+    int with_K[kMaxNodes + 1];
+    std::fill(with_K, with_K + kMaxNodes + 1, -1);
+    h->h_types.reserve(n_types);
     for (int i = 0; i < n_types; ++i) {
         const int nt = p[i].mig_tables > 1 ? p[i].mig_tables : 1;
         const float spread = nt > 1 ? p[i].mig_spread : 0.0f;
@@ -1659,7 +1663,9 @@ static int types_create(const bysdf_type_params* p, int32_t n_types, bysdf_types
         } else {
             ti = it->second;
         }
-        TypeRec r = bysdf_make_rec(p[i]);
+        int& like = with_K[p[i].K];
+        TypeRec r = bysdf_make_rec(p[i], like >= 0 ? &h->h_types[like] : nullptr);
+        if (like < 0) like = i;
         r.table_off = h->h_table_off[ti];
         h->h_types.push_back(r);
         h->h_type_table.push_back(ti);

@@ -19,7 +19,8 @@ template <bool MIG> struct TabPtrT {
 using TabPtr = TabPtrT<true>;
 
 // The device record of one type: its parameters and the derived scalars.
-inline bysdf::TypeRec bysdf_make_rec(const bysdf_type_params& p)
+// same_K (nullable): a record with as many nodes, whose disc points it shares.
+inline bysdf::TypeRec bysdf_make_rec(const bysdf_type_params& p, const bysdf::TypeRec* same_K = nullptr)
 {
     bysdf::TypeRec t;
     memset(&t, 0, sizeof(t));
@@ -50,7 +51,10 @@ inline bysdf::TypeRec bysdf_make_rec(const bysdf_type_params& p)
     t.mig_spread = p.mig_spread;
     t.table_texels = t.mig_tables * p.tex_size;
     bysdf::fill_derived(t);
-    bysdf::fill_node_disk(t);
+    if (same_K)
+        memcpy(t.node_disk, same_K->node_disk, sizeof(t.node_disk));
+    else
+        bysdf::fill_node_disk(t);
     return t;
 }
 
