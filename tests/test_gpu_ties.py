@@ -48,3 +48,26 @@ def test_ties_independent_of_batch(n_yarns, copies):
     p = _run(torch, S, o[order], d[order], tm[order])
     for k in g:
         assert np.array_equal(g[k][order], p[k]), k
+
+
+def test_ties_inside_a_bundle():
+    """Rays that start within a bundle of overlapping yarns: their origins lie
+    in several boxes at once, at equal distances."""
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    rng = np.random.default_rng(2)
+    x = np.linspace(-1.0, 1.0, 24)
+    ctrl = np.concatenate([np.stack([x, rng.uniform(-.1, .1) + 0.02 * np.sin(2 * x),
+                                     rng.uniform(-.1, .1) + 0.02 * np.cos(1.5 * x), np.full_like(x, .05)], 1)
+                           for _ in range(40)]).astype(np.float32)
+    S = bysdf.yarn_scene_create(ctrl, np.arange(41, dtype=np.int64) * 24, np.zeros(40, np.int32),
+                                np.zeros(40, np.float32))
+    n = 200003
+    o = (rng.uniform(-1, 1, (n, 3)) * [1, .12, .12]).astype(np.float32)
+    d = rng.normal(size=(n, 3)).astype(np.float32)
+    tm = np.full(n, 50.0, np.float32)
+    g = _run(torch, S, o, d, tm)
+    order = rng.permutation(n)
+    p = _run(torch, S, o[order], d[order], tm[order])
+    for k in g:
+        assert np.array_equal(g[k][order], p[k]), k
