@@ -198,7 +198,7 @@ def _rows(t, k):
     0.7 us, and an evaluation passes 18 of them (27 us of host time a call
     with views, 11 us without)."""
     if not hasattr(t, "data_ptr"):
-        return [t[i].data_ptr() for i in range(k)]
+        return [_ptr(t[i]) for i in range(k)]
     if t.dim() == 0 or t.shape[0] < k:
         t[k - 1]  # raises as the views did
     base = t.data_ptr()
