@@ -355,8 +355,8 @@ size_t bysdf_backward_workspace_size(int64_t n, int32_t n_types);
  * entries, type_offsets[n_types] == n; q->type_id is not read).  grad_E is
  * a DEVICE float array n x 3 (row-major), grad_theta DEVICE n_types x 8,
  * per_query (nullable) DEVICE n x 8 receives each query's terms.  beta and
- * the twists are differentiated by forward-mode tangents through the whole
- * model (shadowing recomputed, nothing stored by the forward pass); the
+ * the twists are differentiated by one reverse sweep over the recomputed
+ * model (shadowing included, nothing stored by the forward pass); the
  * albedo and the densities enter linearly and use closed forms.  Away from
  * the model's discrete decisions this is the derivative; at a texel centre
  * of the fiber table it is one-sided.  Each tile of at most 256 queries of

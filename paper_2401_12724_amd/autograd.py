@@ -7,7 +7,7 @@ ply density, fiber density).  The forward pass writes theta into the handle
 (bysdf_types_set_theta) and runs bysdf_eval; the backward pass writes the
 same theta back (another forward on the handle may have replaced it) and
 runs bysdf_eval_backward, which recomputes the model (shadowing included)
-with forward-mode tangents, so nothing but the inputs is kept between the
+and sweeps it in reverse, so nothing but the inputs is kept between the
 passes.  The handle clamps theta to its valid ranges (albedo >= 0, beta in
 [1e-4, 10], twists in [-1.5, 1.5] rad, densities in [0, 1]); where a
 component lies strictly outside its range the value does not depend on it

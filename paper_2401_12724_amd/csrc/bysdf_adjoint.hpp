@@ -12,11 +12,11 @@
 // three tangents.  Compared with three forward-mode passes over the whole
 // model, one per parameter, the model's values are formed once instead of
 // three times and no zero tangents are carried: forward and backward of 4 Mi
-// queries (64 types, 3 plies, 4 nodes) take 2.6 ms, 7.0 ms with the passes.
-// The sweep needs about 450 registers, so one wavefront per SIMD runs; VALU
-// issue bounds it (about 5000 instructions a query and two thirds of them
-// FP64), and at two wavefronts the spills cost more than the second hides
-// (4.7 ms).
+// queries (64 types, 3 plies, 4 nodes) take 2.5 ms, 7.3 ms with the passes.
+// The sweep needs 424 registers (up to 4 plies, isotropic, no migration), so
+// one wavefront per SIMD runs; VALU issue bounds it (about 5000 instructions a
+// query and two thirds of them FP64), and at two wavefronts the spills cost
+// more than the second hides (4.7 ms).
 //
 // Branch decisions use the values only (the derivative of the
 // piecewise-smooth model away from its decision boundaries).  Geometry and

@@ -275,7 +275,8 @@ constexpr int kWave = 64;  // wavefront width of gfx950
 // 200-350 B per lane.  With the single-type path of the type waterfall, two
 // wavefronts win for the eval (4.09 ms), the sampler (5.47 -> 4.88 ms), the
 // fused eval + sample (4.43 ms) and the batched eval (20.2 -> 14.7 ms on
-// 2^26 queries); one wins for the adjoint (4 Mi queries: 2.6 ms, 4.7 at two).
+// 2^26 queries); one wins for the adjoint (forward and backward of 4 Mi
+// queries: 2.5 ms, 4.7 at two).
 #ifndef BYSDF_EVAL_MIN_WAVES
 #define BYSDF_EVAL_MIN_WAVES 2
 #endif

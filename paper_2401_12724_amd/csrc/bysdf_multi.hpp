@@ -156,8 +156,8 @@ __host__ __device__ inline bool footprint_geometry(const Derived<G, S>& P, const
 
 // The aggregated frame and shadowing of the footprint in place of a
 // stratum's own.  The lobe weights follow from the frame that stays and are
-// formed after this, once; formed for both frames, and with the output
-// pointers in LDS, the sampler takes 211 us instead of 199 (250,007 queries).
+// formed after this, once: formed for both frames the sampler takes 211 us
+// instead of 199 (250,007 queries).
 template <class G, class S, int MP>
 __host__ __device__ inline void apply_aggregate(XState<G, S, MP>& X, const Frame<G>& F, S Gm)
 {

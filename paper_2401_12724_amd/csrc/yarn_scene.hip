@@ -8,7 +8,7 @@
 // median splits below depth 40, collapsed to four children per node.
 // Spans are stored in leaf order next to their records.
 //
-// Kernel k_intersect: a wavefront takes up to 64 rays and searches 16 at a
+// Kernel k_intersect: a wavefront takes up to 32 rays and searches 16 at a
 // time, four lanes per ray, with an LDS stack per ray ([entry][ray]) of
 // 3 (depth + 1) entries.  A point query
 // first collects the yarns whose tube holds the origin, then the closest

@@ -903,10 +903,10 @@ struct RayHit {
 // The traversal is bound by VALU issue where the chip is full and by the
 // dependent loads of the longest ray where it is not.  Against one lane per
 // ray (a fan of 64 rays waits for its longest; 17 samples of a span in a row
-// for any lane that needs them) a 320 x 180 preview at 4 spp and depth 4
-// takes 2.24 instead of 4.3 ms and a 48 x 48 crop with its gradient at 16 spp
-// 1.00 instead of 3.25 ms; the weave's 2.07 M primary rays take 1.21 instead
-// of 1.24 ms (fewer lanes idle, but rays are set up and finished 32 at a time).
+// for any lane that needs them) a 320 x 180 preview at 4 spp and depth 4 went
+// from 4.24 to 2.18 ms and a 48 x 48 crop with its gradient at 16 spp from
+// 3.35 to 0.98 ms; the weave's 2.07 M primary rays take 1.23 instead of 1.25
+// ms (fewer lanes idle, but rays are set up and finished 32 at a time).
 __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, bool live, double t_min, int& n_ex)
 {
     const int lane = __lane_id(), quad = lane / kQuad, me = quad_lane();
@@ -993,7 +993,8 @@ __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, b
         // from before it: that costs only pruning.  A span that survives the
         // final filter of the candidates (sampled entry within kCandMargin R
         // of the ray's smallest) passes the scan limit whenever it is
-        // scanned, so the hit does not depend on the order.
+        // scanned, and equal entries are settled by met_before, so the hit
+        // does not depend on the order.
         double tb = from_ordered(W.tb[ray]);
         const float t0 = (float)t_min - slack, t1 = (float)tb + slack;
         while (code >= 0) {
@@ -1111,8 +1112,11 @@ __device__ inline RayHit trace_wave(const SceneView& S, WaveRays& W, int* stk, b
 }
 
 // Rays a wavefront takes per visit of its lanes: 32 where that leaves the
-// chip full, 16 for the short queues of late bounces and small batches,
-// whose time is the longest ray's and not the issue rate.
+// chip full (4,096 wavefronts from 131,072 rays on), 16 for the short queues
+// of late bounces and small batches, whose time is the longest ray's and not
+// the issue rate.  Random rays onto a weave of 128 x 128 yarns, 16 and 32 a
+// wavefront: 16,384 rays 148 and 236 us, 131,072 rays 403 and 470, 524,288
+// rays 1343 and 1336, 1,048,576 rays 2567 and 2500.
 __host__ __device__ inline int rays_per_wave(int64_t n) { return n >= 2 * 65536 ? kRays : kWaveRays; }
 
 // Frame, h and arc length at a hit.
